@@ -233,8 +233,7 @@ int encode_compressed(const uint16_t *w_new, const uint8_t *exp_cache,
   a.scan_prefix = use_count_scan(n_elems, l);
   a.exc_tiles_per_wave = exc_tiles_per_wave(tiles, l);
   a.xcd_run_log2 = enc_xcd_runs(tiles, l) ? kXcdRunLog2 : 0u;
-  const bool vec = aligned(w_new, 16) && aligned(exp_cache, 8);
-  return launch_encode(a, vec, stream) == hipSuccess ? CIERA_OK : CIERA_EHIP;
+  return launch_encode(a, stream) == hipSuccess ? CIERA_OK : CIERA_EHIP;
 }
 
 }  // namespace
@@ -262,9 +261,8 @@ int ciera_encode(const uint16_t *w_new, const uint8_t *exp_cache,
       ciera_encoded_bound(n_elems, block_elems, f16 ? CIERA_FP16 : 0))
     return CIERA_ENOSPC;
   if (raw) {
-    const bool vec = aligned(w_new, 16);
     return launch_encode_raw(w_new, n_elems, block_elems,
-                             static_cast<uint8_t *>(out), out_bytes, vec, f16,
+                             static_cast<uint8_t *>(out), out_bytes, f16,
                              stream) == hipSuccess
                ? CIERA_OK
                : CIERA_EHIP;
@@ -292,7 +290,7 @@ int ciera_hash_blocks(const uint16_t *w, uint64_t n_elems,
   a.num_tiles = uint32_t(enc_tiles(n_elems, uint32_t(l)));
   a.tile_elems = enc_tile_elems(uint32_t(l));
   a.hash_out = hash_cache;
-  return launch_hash_blocks(a, aligned(w, 16), stream) == hipSuccess
+  return launch_hash_blocks(a, stream) == hipSuccess
              ? CIERA_OK
              : CIERA_EHIP;
 }
@@ -327,7 +325,7 @@ namespace {
 int decode_args(const void *gathered, uint64_t gathered_bytes,
                 const uint64_t *shard_offsets, uint32_t nshards,
                 uint64_t shard_elems, uint32_t block_elems, uint32_t flags,
-                uint16_t *out, uint8_t *exp_cache, DecArgs *a, bool *vec) {
+                uint16_t *out, uint8_t *exp_cache, DecArgs *a) {
   const int l = log2_block(block_elems);
   if (l < 0) return CIERA_EUNSUPPORTED;
   if (flags & ~CIERA_FP16) return CIERA_EINVAL;
@@ -350,7 +348,6 @@ int decode_args(const void *gathered, uint64_t gathered_bytes,
   a->f16 = f16;
   a->prefix_pass = use_prefix_pass(shard_elems, nshards, l);
   a->xcd_run_log2 = kXcdRunLog2;
-  *vec = (shard_elems % 8 == 0) && aligned(out, 16) && aligned(exp_cache, 8);
   return CIERA_OK;
 }
 
@@ -366,10 +363,9 @@ int ciera_decode_gathered(const void *gathered, uint64_t gathered_bytes,
                           uint64_t workspace_bytes, hipStream_t stream) {
   CallScope scope;
   DecArgs a;
-  bool vec = false;
   const int rc = decode_args(gathered, gathered_bytes, shard_offsets, nshards,
                              shard_elems, block_elems, flags, out, exp_cache,
-                             &a, &vec);
+                             &a);
   if (rc != CIERA_OK) return rc;
   if (!workspace || !aligned(workspace, 16)) return CIERA_EINVAL;
   if (!dec_workspace_ok(shard_elems, nshards, workspace_bytes))
@@ -380,7 +376,7 @@ int ciera_decode_gathered(const void *gathered, uint64_t gathered_bytes,
                     : ans_lists_of(workspace, workspace_bytes, shard_elems,
                                    nshards, int(a.log2B));
   if (launch_ans_decode(a, stream) != hipSuccess) return CIERA_EHIP;
-  return launch_decode(a, vec, stream) == hipSuccess ? CIERA_OK : CIERA_EHIP;
+  return launch_decode(a, stream) == hipSuccess ? CIERA_OK : CIERA_EHIP;
 }
 
 int ciera_update_cache(uint8_t *exp_cache, const void *encoded,
@@ -415,9 +411,8 @@ int ciera_update_cache(uint8_t *exp_cache, const void *encoded,
   a.f16 = f16;
   a.prefix_pass = use_prefix_pass(n_elems, 1, l);
   a.xcd_run_log2 = a.prefix_pass ? kXcdRunLog2 : 0u;
-  const bool vec = aligned(exp_cache, 8);
   if (launch_ans_decode(a, stream) != hipSuccess) return CIERA_EHIP;
-  return launch_decode(a, vec, stream) == hipSuccess ? CIERA_OK : CIERA_EHIP;
+  return launch_decode(a, stream) == hipSuccess ? CIERA_OK : CIERA_EHIP;
 }
 
 int ciera_ans_code(void *encoded, uint64_t n_elems, uint32_t block_elems,
@@ -461,10 +456,9 @@ int ciera_decode_gathered_noalloc(const void *gathered,
                                   uint32_t *err, hipStream_t stream) {
   CallScope scope;
   DecArgs a;
-  bool vec = false;
   const int rc = decode_args(gathered, gathered_bytes, shard_offsets, nshards,
                              shard_elems, block_elems, flags, out, exp_cache,
-                             &a, &vec);
+                             &a);
   if (rc != CIERA_OK) return rc;
   if (!err || !aligned(err, 4)) return CIERA_EINVAL;
   // the tile offsets of every shard must fit in the scratch
@@ -479,7 +473,7 @@ int ciera_decode_gathered_noalloc(const void *gathered,
   a.err = err;
   a.tile_excl = static_cast<uint32_t *>(sp);
   a.ans_exc = nullptr;  // no room for decoded rANS lists: NOSPACE
-  return launch_decode(a, vec, stream) == hipSuccess ? CIERA_OK : CIERA_EHIP;
+  return launch_decode(a, stream) == hipSuccess ? CIERA_OK : CIERA_EHIP;
 }
 
 }  // extern "C"

@@ -224,13 +224,13 @@ struct AnsEncArgs {
 };
 
 // Launchers (ciera_kernels.hip). Each returns the launch status.
-hipError_t launch_encode(const EncArgs &a, bool vec, hipStream_t s);
+hipError_t launch_encode(const EncArgs &a, hipStream_t s);
 // pass 1 with the hash detector only: a.hash_out receives every block's hash
-hipError_t launch_hash_blocks(const EncArgs &a, bool vec, hipStream_t s);
+hipError_t launch_hash_blocks(const EncArgs &a, hipStream_t s);
 hipError_t launch_encode_raw(const uint16_t *w, uint64_t n, uint32_t B,
-                             uint8_t *out, uint64_t *out_bytes, bool vec,
-                             bool f16, hipStream_t s);
-hipError_t launch_decode(const DecArgs &a, bool vec, hipStream_t s);
+                             uint8_t *out, uint64_t *out_bytes, bool f16,
+                             hipStream_t s);
+hipError_t launch_decode(const DecArgs &a, hipStream_t s);
 // ciera_ans.hip
 hipError_t launch_ans_code(const AnsEncArgs &a, hipStream_t s);
 hipError_t launch_ans_decode(const DecArgs &a, hipStream_t s);

@@ -124,8 +124,18 @@ __device__ __forceinline__ uint2 unplane(const uint8_t *g) {
 // Plain stores of the merge's cache patches, for one, left up to 256 MB of
 // them behind a DeepSeek-style decode: the encode after it took 131 instead
 // of 84 us.
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+//
+// The callers' buffers (W', caches, decoded values) may start anywhere: a
+// shard of n values is a slice at j n of a flat buffer, and n need not be a
+// multiple of 8. CDNA4 takes 8- and 16-byte global accesses at any address
+// (the compiler emits the same single instruction for them), so every whole
+// octet goes through these types, which promise no more than the element's
+// own alignment. One kernel then serves every address: 12 shards of
+// 34,963,798 values (encode and gathered decode, two iterations) take 768 us
+// against 2232 us with element-wise accesses for n % 8 != 0, and aligned
+// shards run as before (OLMoE layer encode 23.4 us either way).
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4), aligned(2)));
 
 __device__ __forceinline__ uint2 ld_nt8(const uint8_t *p) {
   const u32x2_t x =
@@ -149,13 +159,31 @@ __device__ __forceinline__ void st_nt16(uint16_t *p, uint4 v) {
   __builtin_nontemporal_store(x, reinterpret_cast<u32x4_t *>(p));
 }
 
+__device__ __forceinline__ uint2 ld8(const uint8_t *p) {
+  const u32x2_t x = *reinterpret_cast<const u32x2_t *>(p);
+  return make_uint2(x.x, x.y);
+}
+
+__device__ __forceinline__ uint4 ld16(const uint16_t *p) {
+  const u32x4_t x = *reinterpret_cast<const u32x4_t *>(p);
+  return make_uint4(x.x, x.y, x.z, x.w);
+}
+
+__device__ __forceinline__ void st8(uint8_t *p, uint2 v) {
+  const u32x2_t x = {v.x, v.y};
+  *reinterpret_cast<u32x2_t *>(p) = x;
+}
+
+__device__ __forceinline__ void st16(uint16_t *p, uint4 v) {
+  const u32x4_t x = {v.x, v.y, v.z, v.w};
+  *reinterpret_cast<u32x4_t *>(p) = x;
+}
+
 // ------------------------------------------------- octet loads and stores --
-// `valid` is the number of in-range values of the octet (1..8). VEC means the
-// base pointers are aligned for vector accesses; the ragged last octet and
-// unaligned callers take the element-wise path.
-template <bool VEC>
+// `valid` is the number of in-range values of the octet (1..8); the ragged
+// last octet of a shard goes element by element.
 __device__ __forceinline__ uint4 load_w8(const uint16_t *p, uint32_t valid) {
-  if (VEC && valid == 8) return *reinterpret_cast<const uint4 *>(p);
+  if (valid == 8) return ld16(p);
   uint32_t v[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
   for (uint32_t i = 0; i < 8; ++i)
@@ -164,17 +192,15 @@ __device__ __forceinline__ uint4 load_w8(const uint16_t *p, uint32_t valid) {
 }
 
 // load_w8 for the encode's second read of W' (non-temporal: its last use)
-template <bool VEC>
 __device__ __forceinline__ uint4 reread_w8(const uint16_t *p, uint32_t valid) {
-  if (VEC && valid == 8) return ld_nt16(p);
-  return load_w8<VEC>(p, valid);
+  if (valid == 8) return ld_nt16(p);
+  return load_w8(p, valid);
 }
 
-template <bool VEC>
 __device__ __forceinline__ void store_w8(uint16_t *p, uint4 v,
                                          uint32_t valid) {
-  if (VEC && valid == 8) {
-    *reinterpret_cast<uint4 *>(p) = v;
+  if (valid == 8) {
+    st16(p, v);
     return;
   }
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -183,9 +209,8 @@ __device__ __forceinline__ void store_w8(uint16_t *p, uint4 v,
     if (i < valid) p[i] = uint16_t(w[i >> 1] >> ((i & 1) * 16));
 }
 
-template <bool VEC>
 __device__ __forceinline__ uint2 load_b8(const uint8_t *p, uint32_t valid) {
-  if (VEC && valid == 8) return *reinterpret_cast<const uint2 *>(p);
+  if (valid == 8) return ld8(p);
   uint32_t v[2] = {0u, 0u};
 #pragma unroll
   for (uint32_t i = 0; i < 8; ++i)
@@ -193,10 +218,9 @@ __device__ __forceinline__ uint2 load_b8(const uint8_t *p, uint32_t valid) {
   return make_uint2(v[0], v[1]);
 }
 
-template <bool VEC>
 __device__ __forceinline__ void store_b8(uint8_t *p, uint2 v, uint32_t valid) {
-  if (VEC && valid == 8) {
-    *reinterpret_cast<uint2 *>(p) = v;
+  if (valid == 8) {
+    st8(p, v);
     return;
   }
   const uint32_t w[2] = {v.x, v.y};
@@ -343,7 +367,7 @@ enum : int { kDetExact = 0, kDetHash = 1, kDetHashOnly = 2 };
 // loads are non-temporal, while the cache bytes are loaded plainly for the
 // exception pass to find again. Without it the exception pass re-reads W'
 // and the cache is read once: the other way round.
-template <bool VEC, bool ELEMS, int DET, bool F16 = false, bool NTW = false>
+template <bool ELEMS, int DET, bool F16 = false, bool NTW = false>
 __global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
   constexpr bool HASH = DET != kDetExact;
   constexpr bool OUT = DET != kDetHashOnly;
@@ -516,19 +540,17 @@ __global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
   for (uint64_t cbase = tbase; cbase < tbase + T; cbase += kEncChunk) {
     uint32_t mask[8];  // change bits of the lane's octets
     uint64_t ta[8], tb[8];  // block-hash terms of the lane's octets
-    if (VEC && cbase + kEncChunk <= n) {
+    if (cbase + kEncChunk <= n) {
       uint4 wv[8];
       uint2 cv[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         wv[u] = NTW ? ld_nt16(a.w + cbase + (uint64_t(u) * 64 + lane) * 8)
-                    : *reinterpret_cast<const uint4 *>(
-                          a.w + cbase + (uint64_t(u) * 64 + lane) * 8);
+                    : ld16(a.w + cbase + (uint64_t(u) * 64 + lane) * 8);
       if (!HASH) {
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          cv[u] = NTW ? *reinterpret_cast<const uint2 *>(
-                            a.cache + cbase + (uint64_t(u) * 64 + lane) * 8)
+          cv[u] = NTW ? ld8(a.cache + cbase + (uint64_t(u) * 64 + lane) * 8)
                       : ld_nt8(a.cache + cbase + (uint64_t(u) * 64 + lane) * 8);
       }
 #pragma unroll
@@ -557,8 +579,7 @@ __global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
                              (bytes_ne4(e.y, cv[u].y) << 4))
                           : uint32_t((e.x != cv[u].x) || (e.y != cv[u].y));
           // the sender's cache brought forward: only octets that differ
-          if (a.cache_out && mask[u])
-            *reinterpret_cast<uint2 *>(a.cache_out + elem) = e;
+          if (a.cache_out && mask[u]) st8(a.cache_out + elem, e);
         }
       }
     } else {
@@ -569,7 +590,7 @@ __global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
         mask[u] = 0;
         uint64_t word = 0;
         if (valid) {
-          const uint4 wv = load_w8<VEC>(a.w + elem, valid);
+          const uint4 wv = load_w8(a.w + elem, valid);
           uint2 e, sm;
           if (F16) {
             // load_w8 zero-fills past n: those fields are 0 in the planes
@@ -584,18 +605,18 @@ __global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
             split4(wv.x, wv.y, e.x, sm.x);
             split4(wv.z, wv.w, e.y, sm.y);
           }
-          if (OUT) store_b8<VEC>(sm_out + elem, sm, valid);
+          if (OUT) store_b8(sm_out + elem, sm, valid);
           if (HASH) {
             // load_w8 zero-fills past n: those bytes are 0 in the word
             word = uint64_t(e.x) | (uint64_t(e.y) << 32);
           } else {
-            const uint2 cv = load_b8<VEC>(a.cache + elem, valid);
+            const uint2 cv = load_b8(a.cache + elem, valid);
             // padding values are 0 with a cached 0: never a change
             mask[u] = ELEMS ? (bytes_ne4(e.x, cv.x) |
                                (bytes_ne4(e.y, cv.y) << 4))
                             : uint32_t((e.x != cv.x) || (e.y != cv.y));
             if (a.cache_out && mask[u])
-              store_b8<VEC>(a.cache_out + elem, e, valid);
+              store_b8(a.cache_out + elem, e, valid);
           }
         }
         if (HASH) hash_terms(uint32_t(u), cbase, word, ta[u], tb[u]);
@@ -779,17 +800,17 @@ __device__ __forceinline__ uint32_t popc_bytes_part(const uint8_t *bmp,
 
 // The exponents of one octet (e: one byte per value) at exception index pos:
 // bf16 bytes at pos, fp16 five bit-plane bytes at 5 (pos / 8).
-template <bool VEC, bool F16>
+template <bool F16>
 __device__ __forceinline__ void put_exc_exps(uint8_t *exc_out, uint64_t pos,
                                              uint2 e, uint32_t valid) {
   if (F16) {
     uint8_t *g = exc_out + 5 * (pos >> 3);
 #pragma unroll
     for (uint32_t q = 0; q < 5; ++q) g[q] = uint8_t(plane_byte(e.x, e.y, q));
-  } else if (VEC && valid == 8) {
+  } else if (valid == 8) {
     st_nt8(exc_out + pos, e);
   } else {
-    store_b8<VEC>(exc_out + pos, e, valid);
+    store_b8(exc_out + pos, e, valid);
   }
 }
 
@@ -798,16 +819,16 @@ __device__ __forceinline__ void put_exc_exps(uint8_t *exc_out, uint64_t pos,
 // pass 1 has already written the new exponent of every changed value into
 // the cache, and every other value of a changed block was unchanged, so the
 // cache holds exp(W') for the whole block: 8 bytes an octet.
-template <bool VEC, bool F16, bool FROMC>
+template <bool F16, bool FROMC>
 struct ExcSrc {
   using T = typename std::conditional<FROMC, uint2, uint4>::type;
   __device__ static __forceinline__ T load(const EncArgs &a, uint64_t elem,
                                            uint32_t valid) {
     if constexpr (FROMC) {
-      if (VEC && valid == 8) return ld_nt8(a.cache_out + elem);
-      return load_b8<VEC>(a.cache_out + elem, valid);
+      if (valid == 8) return ld_nt8(a.cache_out + elem);
+      return load_b8(a.cache_out + elem, valid);
     } else {
-      return reread_w8<VEC>(a.w + elem, valid);
+      return reread_w8(a.w + elem, valid);
     }
   }
   __device__ static __forceinline__ uint2 exps(const T &v) {
@@ -898,10 +919,10 @@ __device__ __forceinline__ uint32_t sum_words_part(const uint32_t *c,
 // list: the per-tile counts of pass 1 in front of the tile, summed here by
 // the workgroup, or (a.scan_prefix) read from their scan. The last tile
 // writes the header. W' is read again only where the bitmap says so.
-template <bool VEC, bool FROMC>
+template <bool FROMC>
 __global__ __launch_bounds__(kThreads) void encode_exc_elems_kernel(
     EncArgs a) {
-  using Src = ExcSrc<VEC, false, FROMC>;
+  using Src = ExcSrc<false, FROMC>;
   __shared__ uint32_t s_red[4];
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t nt = a.num_tiles;
@@ -969,9 +990,9 @@ __global__ __launch_bounds__(kThreads) void encode_exc_elems_kernel(
 // so that that many reads of the rows' exponents are in flight per wave; the
 // first batch is issued before the offset of the run (the changed blocks in
 // front of it) is counted, and the two overlap.
-template <bool VEC, bool F16, bool FROMC, uint32_t D>
+template <bool F16, bool FROMC, uint32_t D>
 __global__ __launch_bounds__(kThreads) void encode_exc_rows_kernel(EncArgs a) {
-  using Src = ExcSrc<VEC, F16, FROMC>;
+  using Src = ExcSrc<F16, FROMC>;
   __shared__ uint32_t s_red[4];
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t n = a.n;
@@ -1058,7 +1079,7 @@ __global__ __launch_bounds__(kThreads) void encode_exc_rows_kernel(EncArgs a) {
         const uint32_t valid = octet_valid(elem, n);
         const uint64_t pos = ((out_row + d) << 9) + uint64_t(lane) * 8;
         if (valid && pos + valid <= n)
-          put_exc_exps<VEC, F16>(exc_out, pos, Src::exps(wv[d]), valid);
+          put_exc_exps<F16>(exc_out, pos, Src::exps(wv[d]), valid);
       }
     }
     out_row += cnt;
@@ -1087,10 +1108,10 @@ __global__ __launch_bounds__(kThreads) void encode_exc_rows_kernel(EncArgs a) {
 // and copies them kExcBatch instructions at a time: the work follows the
 // changed blocks, not the shard. The first batch is issued before the
 // offset count of the run, and the two overlap.
-template <bool VEC, bool F16, bool FROMC>
+template <bool F16, bool FROMC>
 __global__ __launch_bounds__(kThreads) void encode_exc_blocks_kernel(
     EncArgs a) {
-  using Src = ExcSrc<VEC, F16, FROMC>;
+  using Src = ExcSrc<F16, FROMC>;
   constexpr uint32_t D = kExcBatch;
   __shared__ uint32_t s_red[4];
   __shared__ uint32_t s_list[4][64];  // a wave's changed blocks of a chunk
@@ -1183,7 +1204,7 @@ __global__ __launch_bounds__(kThreads) void encode_exc_blocks_kernel(
       if (valid[d]) {
         const uint64_t pos = ((out_blk + kk[d] - r) << log2B) + in_blk;
         if (pos + valid[d] <= n)
-          put_exc_exps<VEC, F16>(exc_out, pos, Src::exps(wv[d]), valid[d]);
+          put_exc_exps<F16>(exc_out, pos, Src::exps(wv[d]), valid[d]);
       }
     }
     out_blk += taken;
@@ -1206,7 +1227,6 @@ __global__ __launch_bounds__(kThreads) void encode_exc_blocks_kernel(
 }
 
 // Raw form: header + the values unchanged. One octet per lane.
-template <bool VEC>
 __global__ __launch_bounds__(kThreads) void encode_raw_kernel(
     const uint16_t *w, uint64_t n, uint32_t B, uint8_t *out,
     uint64_t *out_bytes, uint32_t dtype) {
@@ -1217,7 +1237,7 @@ __global__ __launch_bounds__(kThreads) void encode_raw_kernel(
   if (o < octets) {
     const uint64_t elem = o * 8;
     const uint32_t valid = octet_valid(elem, n);
-    store_w8<VEC>(body + elem, load_w8<VEC>(w + elem, valid), valid);
+    store_w8(body + elem, load_w8(w + elem, valid), valid);
   }
   if (blockIdx.x == 0) {
     const uint32_t tid = threadIdx.x;
@@ -1371,9 +1391,9 @@ __global__ __launch_bounds__(kScanThreads) void tile_prefix_kernel(DecArgs a) {
 // UPDATE_ONLY: the ExpCache patch alone (no sign+mantissa, no output).
 // A whole tile issues its loads in two batches (sign|mantissa bytes together
 // with the bitmap words, then one cache-or-exception load per octet, chosen
-// by address rather than by branch); the ragged last tile and unaligned
-// buffers go element by element.
-template <int OCT, bool VEC, bool UPDATE_ONLY, bool F16 = false>
+// by address rather than by branch); the ragged last tile goes octet by
+// octet.
+template <int OCT, bool UPDATE_ONLY, bool F16 = false>
 __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
   constexpr uint32_t T = kThreads * 8 * OCT;
   // tile bitmap words (32 blocks each) covering at most T/16 blocks + 1 word
@@ -1411,7 +1431,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
   if (!sv.ok) return;
   const uint64_t n = a.n;
   if (base >= n) return;
-  const bool full = VEC && base + T <= n;
+  const bool full = base + T <= n;
   uint8_t *const cache = a.cache + uint64_t(j) * n;
   uint16_t *const out = UPDATE_ONLY ? nullptr : a.out + uint64_t(j) * n;
 
@@ -1422,8 +1442,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
       uint4 wv[OCT];
 #pragma unroll
       for (int u = 0; u < OCT; ++u)
-        wv[u] = *reinterpret_cast<const uint4 *>(
-            body + base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+        wv[u] = ld16(body + base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
 #pragma unroll
       for (int u = 0; u < OCT; ++u) {
         const uint64_t elem =
@@ -1436,8 +1455,8 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
           split4(wv[u].x, wv[u].y, e.x, sm.x);
           split4(wv[u].z, wv[u].w, e.y, sm.y);
         }
-        if (!UPDATE_ONLY) *reinterpret_cast<uint4 *>(out + elem) = wv[u];
-        *reinterpret_cast<uint2 *>(cache + elem) = e;
+        if (!UPDATE_ONLY) st16(out + elem, wv[u]);
+        st8(cache + elem, e);
       }
       return;
     }
@@ -1447,8 +1466,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
       const uint64_t elem = base + uint64_t(o) * 8u;
       const uint32_t valid = octet_valid(elem, n);
       if (!valid) continue;
-      // the raw body is 16-byte aligned whenever the shard is
-      const uint4 wv = load_w8<true>(body + elem, valid);
+      const uint4 wv = load_w8(body + elem, valid);
       uint2 e, sm, hi;
       if (F16) {
         split4_f16(wv.x, wv.y, e.x, sm.x, hi.x);
@@ -1457,8 +1475,8 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
         split4(wv.x, wv.y, e.x, sm.x);
         split4(wv.z, wv.w, e.y, sm.y);
       }
-      if (!UPDATE_ONLY) store_w8<VEC>(out + elem, wv, valid);
-      store_b8<VEC>(cache + elem, e, valid);
+      if (!UPDATE_ONLY) store_w8(out + elem, wv, valid);
+      store_b8(cache + elem, e, valid);
     }
     return;
   }
@@ -1475,7 +1493,6 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
   uint2 smv[OCT], hiv[OCT];
   if (F16 && !UPDATE_ONLY) {
     if (full) {
-      // n % 8 == 0 on this path, so the tile's planes are 8-byte aligned;
       // the barriers of the prefix sum below order these stores
       const uint8_t *hp = sm_in + n + 3 * (base >> 3);
       for (uint32_t i = tid; i < kHiPairs; i += kThreads)
@@ -1503,7 +1520,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
             base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u;
         const uint32_t valid = octet_valid(elem, n);
         smv[u] =
-            valid ? load_b8<true>(sm_in + elem, valid) : make_uint2(0u, 0u);
+            valid ? load_b8(sm_in + elem, valid) : make_uint2(0u, 0u);
       }
     }
   }
@@ -1592,14 +1609,14 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
       else if (!UPDATE_ONLY)
         ev[u] = ld_nt8(src[u]);
       else if (ch[u])  // the cache update alone: plain loads measured faster
-        ev[u] = *reinterpret_cast<const uint2 *>(src[u]);
+        ev[u] = ld8(src[u]);
     }
 #pragma unroll
     for (int u = 0; u < OCT; ++u) {
       const uint64_t elem = base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u;
       if (ch[u]) {
         if (UPDATE_ONLY)
-          *reinterpret_cast<uint2 *>(cache + elem) = ev[u];
+          st8(cache + elem, ev[u]);
         else  // the merge's patches: non-temporal, like its other streams
           st_nt8(cache + elem, ev[u]);
       }
@@ -1638,11 +1655,11 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
           continue;
         }
         ev = F16 ? unplane<5>(exc + 5 * (pos >> 3))
-                 : load_b8<true>(exc + pos, valid);
-        store_b8<VEC>(cache + elem, ev, valid);
+                 : load_b8(exc + pos, valid);
+        store_b8(cache + elem, ev, valid);
       } else {
         if (UPDATE_ONLY) continue;
-        ev = load_b8<VEC>(cache + elem, valid);
+        ev = load_b8(cache + elem, valid);
       }
       if (!UPDATE_ONLY) {
         uint4 wv;
@@ -1653,7 +1670,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
           merge4(ev.x, smv[u].x, wv.x, wv.y);
           merge4(ev.y, smv[u].y, wv.z, wv.w);
         }
-        store_w8<VEC>(out + elem, wv, valid);
+        store_w8(out + elem, wv, valid);
       }
     }
   }
@@ -1728,7 +1745,7 @@ __global__ __launch_bounds__(kThreads) void count_tile_bits_kernel(
 
 // Decode, B = 1, step 2 (step 3 after a scan of the counts): patch and merge
 // (UPDATE_ONLY: patch only).
-template <int OCT, bool VEC, bool UPDATE_ONLY>
+template <int OCT, bool UPDATE_ONLY>
 __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
   constexpr uint32_t T = kThreads * 8 * OCT;
   __shared__ uint32_t s_seg[4 * OCT + 1];
@@ -1753,12 +1770,12 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
       const uint64_t elem = base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u;
       const uint32_t valid = octet_valid(elem, n);
       if (!valid) continue;
-      const uint4 wv = load_w8<true>(body + elem, valid);
+      const uint4 wv = load_w8(body + elem, valid);
       uint2 e, sm;
       split4(wv.x, wv.y, e.x, sm.x);
       split4(wv.z, wv.w, e.y, sm.y);
-      if (!UPDATE_ONLY) store_w8<VEC>(out + elem, wv, valid);
-      store_b8<VEC>(cache + elem, e, valid);
+      if (!UPDATE_ONLY) store_w8(out + elem, wv, valid);
+      store_b8(cache + elem, e, valid);
     }
     return;
   }
@@ -1767,7 +1784,7 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
   const uint8_t *const bmp = sm_in + pad16(n);
   const uint8_t *const exc = bmp + pad16((n + 7) / 8);
   const uint32_t tiles = uint32_t(dec_tiles(n));
-  const bool full = VEC && base + T <= n;
+  const bool full = base + T <= n;
 
   uint32_t mask[OCT], cnt[OCT];
   uint2 smv[OCT], ev[OCT];
@@ -1782,14 +1799,13 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
       // streams this call touches once: non-temporal, as in decode_kernel
       // (the cache update alone keeps plain loads there too)
       if (!UPDATE_ONLY) smv[u] = ld_nt8(sm_in + elem);
-      ev[u] = UPDATE_ONLY ? *reinterpret_cast<const uint2 *>(cache + elem)
-                          : ld_nt8(cache + elem);
+      ev[u] = UPDATE_ONLY ? ld8(cache + elem) : ld_nt8(cache + elem);
     } else {
       smv[u] = make_uint2(0u, 0u);
       ev[u] = make_uint2(0u, 0u);
       if (valid) {
-        if (!UPDATE_ONLY) smv[u] = load_b8<true>(sm_in + elem, valid);
-        ev[u] = load_b8<VEC>(cache + elem, valid);
+        if (!UPDATE_ONLY) smv[u] = load_b8(sm_in + elem, valid);
+        ev[u] = load_b8(cache + elem, valid);
       }
     }
   }
@@ -1824,7 +1840,7 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
       if (!UPDATE_ONLY && full)
         st_nt8(cache + elem, ev[u]);
       else
-        store_b8<VEC>(cache + elem, ev[u], valid);
+        store_b8(cache + elem, ev[u], valid);
     }
     if (!UPDATE_ONLY) {
       uint4 wv;
@@ -1833,7 +1849,7 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
       if (full)
         st_nt16(out + elem, wv);
       else
-        store_w8<VEC>(out + elem, wv, valid);
+        store_w8(out + elem, wv, valid);
     }
   }
   if (bad) set_error(a.err, CIERA_DEVERR_BOUNDS);
@@ -1852,63 +1868,51 @@ namespace {
 template <bool B>
 using bool_c = std::integral_constant<bool, B>;
 
-// Launch the exception-pass kernel that pick(vec, f16, from_cache) names,
-// with the three flags as template arguments (f16 is always false at B = 1).
+// Launch the exception-pass kernel that pick(f16, from_cache) names, with the
+// two flags as template arguments (f16 is always false at B = 1).
 template <bool ELEMS, typename Pick>
-void launch_exc(dim3 grid, const EncArgs &a, bool vec, bool f16, bool fromc,
+void launch_exc(dim3 grid, const EncArgs &a, bool f16, bool fromc,
                 hipStream_t s, Pick pick) {
-  auto go = [&](auto v, auto f, auto c) {
-    hipLaunchKernelGGL(pick(v, f, c), grid, dim3(kThreads), 0, s, a);
+  auto go = [&](auto f, auto c) {
+    hipLaunchKernelGGL(pick(f, c), grid, dim3(kThreads), 0, s, a);
   };
-  auto with_c = [&](auto v, auto f) {
-    if (fromc) go(v, f, bool_c<true>{}); else go(v, f, bool_c<false>{});
+  auto with_c = [&](auto f) {
+    if (fromc) go(f, bool_c<true>{}); else go(f, bool_c<false>{});
   };
-  auto with_f = [&](auto v) {
-    if (!ELEMS && f16) with_c(v, bool_c<!ELEMS>{});
-    else with_c(v, bool_c<false>{});
-  };
-  if (vec) with_f(bool_c<true>{}); else with_f(bool_c<false>{});
+  if (!ELEMS && f16) with_c(bool_c<!ELEMS>{});
+  else with_c(bool_c<false>{});
 }
 }  // namespace
 
-hipError_t launch_encode(const EncArgs &a, bool vec, hipStream_t s) {
+hipError_t launch_encode(const EncArgs &a, hipStream_t s) {
   const dim3 grid((a.num_tiles + 3) / 4), block(kThreads);
   const bool elems = a.log2B == 0;
   // with the fused cache update the exception pass reads the cache, not W'
   const bool fromc = a.cache_out != nullptr;
-  auto exact = [&](auto v, auto e, auto f) {
-    constexpr bool V = decltype(v)::value, E = decltype(e)::value,
-                   F = decltype(f)::value;
+  auto exact = [&](auto e, auto f) {
+    constexpr bool E = decltype(e)::value, F = decltype(f)::value;
     if (fromc)
-      hipLaunchKernelGGL((encode_pass_kernel<V, E, kDetExact, F, true>), grid,
+      hipLaunchKernelGGL((encode_pass_kernel<E, kDetExact, F, true>), grid,
                          block, 0, s, a);
     else
-      hipLaunchKernelGGL((encode_pass_kernel<V, E, kDetExact, F, false>),
-                         grid, block, 0, s, a);
+      hipLaunchKernelGGL((encode_pass_kernel<E, kDetExact, F, false>), grid,
+                         block, 0, s, a);
   };
-  if (elems) {
-    if (vec) exact(bool_c<true>{}, bool_c<true>{}, bool_c<false>{});
-    else exact(bool_c<false>{}, bool_c<true>{}, bool_c<false>{});
-  } else if (a.f16) {
-    if (vec) exact(bool_c<true>{}, bool_c<false>{}, bool_c<true>{});
-    else exact(bool_c<false>{}, bool_c<false>{}, bool_c<true>{});
-  } else if (a.hashed) {
-    if (vec)
-      hipLaunchKernelGGL((encode_pass_kernel<true, false, kDetHash>), grid,
-                         block, 0, s, a);
-    else
-      hipLaunchKernelGGL((encode_pass_kernel<false, false, kDetHash>), grid,
-                         block, 0, s, a);
-  } else {
-    if (vec) exact(bool_c<true>{}, bool_c<false>{}, bool_c<false>{});
-    else exact(bool_c<false>{}, bool_c<false>{}, bool_c<false>{});
-  }
+  if (elems)
+    exact(bool_c<true>{}, bool_c<false>{});
+  else if (a.f16)
+    exact(bool_c<false>{}, bool_c<true>{});
+  else if (a.hashed)
+    hipLaunchKernelGGL((encode_pass_kernel<false, kDetHash>), grid, block, 0,
+                       s, a);
+  else
+    exact(bool_c<false>{}, bool_c<false>{});
   if (a.scan_prefix)
     hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(kScanThreads), 0, s,
                        a.counts, a.num_tiles, uint64_t(0));
   if (elems) {
-    launch_exc<true>(grid, a, vec, false, fromc, s, [](auto v, auto, auto c) {
-      return encode_exc_elems_kernel<decltype(v)::value, decltype(c)::value>;
+    launch_exc<true>(grid, a, false, fromc, s, [](auto, auto c) {
+      return encode_exc_elems_kernel<decltype(c)::value>;
     });
     return hipGetLastError();
   }
@@ -1920,63 +1924,46 @@ hipError_t launch_encode(const EncArgs &a, bool vec, hipStream_t s) {
                          r.exc_tiles_per_wave;
   const dim3 rgrid(uint32_t((waves + 3) / 4));
   if (r.log2B < 9)
-    launch_exc<false>(rgrid, r, vec, r.f16, fromc, s,
-                      [](auto v, auto f, auto c) {
-                        return encode_exc_blocks_kernel<decltype(v)::value,
-                                                        decltype(f)::value,
-                                                        decltype(c)::value>;
-                      });
+    launch_exc<false>(rgrid, r, r.f16, fromc, s, [](auto f, auto c) {
+      return encode_exc_blocks_kernel<decltype(f)::value, decltype(c)::value>;
+    });
   else if (fromc && r.exc_tiles_per_wave >= 2)
-    launch_exc<false>(rgrid, r, vec, r.f16, fromc, s,
-                      [](auto v, auto f, auto c) {
-                        return encode_exc_rows_kernel<
-                            decltype(v)::value, decltype(f)::value,
-                            decltype(c)::value, kExcBatchDeep>;
-                      });
+    launch_exc<false>(rgrid, r, r.f16, fromc, s, [](auto f, auto c) {
+      return encode_exc_rows_kernel<decltype(f)::value, decltype(c)::value,
+                                    kExcBatchDeep>;
+    });
   else
-    launch_exc<false>(rgrid, r, vec, r.f16, fromc, s,
-                      [](auto v, auto f, auto c) {
-                        return encode_exc_rows_kernel<
-                            decltype(v)::value, decltype(f)::value,
-                            decltype(c)::value, kExcBatch>;
-                      });
+    launch_exc<false>(rgrid, r, r.f16, fromc, s, [](auto f, auto c) {
+      return encode_exc_rows_kernel<decltype(f)::value, decltype(c)::value,
+                                    kExcBatch>;
+    });
   return hipGetLastError();
 }
 
-hipError_t launch_hash_blocks(const EncArgs &a, bool vec, hipStream_t s) {
-  const dim3 grid((a.num_tiles + 3) / 4), block(kThreads);
-  if (vec)
-    hipLaunchKernelGGL((encode_pass_kernel<true, false, kDetHashOnly>), grid,
-                       block, 0, s, a);
-  else
-    hipLaunchKernelGGL((encode_pass_kernel<false, false, kDetHashOnly>), grid,
-                       block, 0, s, a);
+hipError_t launch_hash_blocks(const EncArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL((encode_pass_kernel<false, kDetHashOnly>),
+                     dim3((a.num_tiles + 3) / 4), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_encode_raw(const uint16_t *w, uint64_t n, uint32_t B,
-                             uint8_t *out, uint64_t *out_bytes, bool vec,
-                             bool f16, hipStream_t s) {
+                             uint8_t *out, uint64_t *out_bytes, bool f16,
+                             hipStream_t s) {
   const uint32_t dtype = f16 ? kDtypeFp16 : kDtypeBf16;
   const uint64_t octets = (n + 7) / 8;
   uint64_t blocks = (octets + kThreads - 1) / kThreads;
   if (blocks == 0) blocks = 1;
-  if (vec)
-    hipLaunchKernelGGL((encode_raw_kernel<true>), dim3(uint32_t(blocks)),
-                       dim3(kThreads), 0, s, w, n, B, out, out_bytes,
-                       dtype);
-  else
-    hipLaunchKernelGGL((encode_raw_kernel<false>), dim3(uint32_t(blocks)),
-                       dim3(kThreads), 0, s, w, n, B, out, out_bytes,
-                       dtype);
+  hipLaunchKernelGGL(encode_raw_kernel, dim3(uint32_t(blocks)),
+                     dim3(kThreads), 0, s, w, n, B, out, out_bytes, dtype);
   return hipGetLastError();
 }
 
-hipError_t launch_decode(const DecArgs &a, bool vec, hipStream_t s) {
+hipError_t launch_decode(const DecArgs &a, hipStream_t s) {
   const uint64_t tiles = dec_tiles(a.n);
   if (tiles == 0 || a.nshards == 0) return hipSuccess;
   const dim3 grid(uint32_t(tiles), a.nshards), block(kThreads);
   const bool upd = a.out == nullptr;
+  constexpr int O = int(kDecOct);
   if (a.log2B == 0) {
     const dim3 cgrid(uint32_t((tiles + 3) / 4), a.nshards);
     hipLaunchKernelGGL(count_tile_bits_kernel, cgrid, block, 0, s, a,
@@ -1985,60 +1972,27 @@ hipError_t launch_decode(const DecArgs &a, bool vec, hipStream_t s) {
       hipLaunchKernelGGL(scan_counts_kernel, dim3(a.nshards),
                          dim3(kScanThreads), 0, s, a.tile_excl,
                          uint32_t(tiles), dec_count_stride(tiles));
-    constexpr int O = int(kDecOct);
-    if (upd) {
-      if (vec)
-        hipLaunchKernelGGL((decode_elems_kernel<O, true, true>), grid, block,
-                           0, s, a);
-      else
-        hipLaunchKernelGGL((decode_elems_kernel<O, false, true>), grid, block,
-                           0, s, a);
-    } else {
-      if (vec)
-        hipLaunchKernelGGL((decode_elems_kernel<O, true, false>), grid, block,
-                           0, s, a);
-      else
-        hipLaunchKernelGGL((decode_elems_kernel<O, false, false>), grid,
-                           block, 0, s, a);
-    }
+    if (upd)
+      hipLaunchKernelGGL((decode_elems_kernel<O, true>), grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL((decode_elems_kernel<O, false>), grid, block, 0, s,
+                         a);
     return hipGetLastError();
   }
   if (a.prefix_pass)
     hipLaunchKernelGGL(tile_prefix_kernel, dim3(a.nshards), dim3(kScanThreads),
                        0, s, a);
   if (a.f16) {
-    constexpr int O = int(kDecOct);
-    if (upd) {
-      if (vec)
-        hipLaunchKernelGGL((decode_kernel<O, true, true, true>), grid, block,
-                           0, s, a);
-      else
-        hipLaunchKernelGGL((decode_kernel<O, false, true, true>), grid, block,
-                           0, s, a);
-    } else {
-      if (vec)
-        hipLaunchKernelGGL((decode_kernel<O, true, false, true>), grid, block,
-                           0, s, a);
-      else
-        hipLaunchKernelGGL((decode_kernel<O, false, false, true>), grid,
-                           block, 0, s, a);
-    }
-    return hipGetLastError();
-  }
-  if (upd) {
-    if (vec)
-      hipLaunchKernelGGL((decode_kernel<int(kDecOct), true, true>), grid,
-                         block, 0, s, a);
+    if (upd)
+      hipLaunchKernelGGL((decode_kernel<O, true, true>), grid, block, 0, s, a);
     else
-      hipLaunchKernelGGL((decode_kernel<int(kDecOct), false, true>), grid,
-                         block, 0, s, a);
+      hipLaunchKernelGGL((decode_kernel<O, false, true>), grid, block, 0, s,
+                         a);
   } else {
-    if (vec)
-      hipLaunchKernelGGL((decode_kernel<int(kDecOct), true, false>), grid,
-                         block, 0, s, a);
+    if (upd)
+      hipLaunchKernelGGL((decode_kernel<O, true>), grid, block, 0, s, a);
     else
-      hipLaunchKernelGGL((decode_kernel<int(kDecOct), false, false>), grid,
-                         block, 0, s, a);
+      hipLaunchKernelGGL((decode_kernel<O, false>), grid, block, 0, s, a);
   }
   return hipGetLastError();
 }
