@@ -75,8 +75,11 @@ constexpr uint64_t kPrefixPassBytes = uint64_t(128) << 20;
 // At 6,144 tiles (25.2M values) that re-reads 19 MB and beats the scan's
 // launch by 2 us per call (26.1 against 28.2 us for the whole encode).
 bool use_count_scan(uint64_t n, uint32_t l) {
-  const uint64_t tiles = enc_tiles(n, l);
+  const uint64_t tiles = enc_tiles(n);
   if (l == 0) return ((tiles + 3) / 4) * tiles * 2 > kPrefixPassBytes;
+  // B > 512: the bitmap is at most 512 KB (n < 2^32), and 2048 workgroups
+  // reading half of it from L2 stay below 2% of such a call
+  if (l > 9) return false;
   const uint64_t per_group = 4 * uint64_t(exc_tiles_per_wave(tiles, l));
   const uint64_t groups = (tiles + per_group - 1) / per_group;
   return groups * bitmap_bytes(n, l) / 2 > kPrefixPassBytes;
@@ -211,7 +214,7 @@ int encode_compressed(const uint16_t *w_new, const uint8_t *exp_cache,
                       uint64_t workspace_bytes, hipStream_t stream,
                       bool hashed, bool f16) {
   if (!workspace || !aligned(workspace, 16)) return CIERA_EINVAL;
-  const uint64_t tiles = enc_tiles(n_elems, l);
+  const uint64_t tiles = enc_tiles(n_elems);
   if (workspace_bytes < enc_ws_bytes(n_elems, l)) return CIERA_ENOSPC;
   EncArgs a{};
   a.w = w_new;
@@ -220,7 +223,6 @@ int encode_compressed(const uint16_t *w_new, const uint8_t *exp_cache,
   a.n = n_elems;
   a.log2B = l;
   a.num_tiles = uint32_t(tiles);
-  a.tile_elems = enc_tile_elems(l);
   a.out = static_cast<uint8_t *>(out);
   a.out_bytes = out_bytes;
   a.ctl = static_cast<WsCtl *>(workspace);
@@ -233,6 +235,11 @@ int encode_compressed(const uint16_t *w_new, const uint8_t *exp_cache,
   a.scan_prefix = use_count_scan(n_elems, l);
   a.exc_tiles_per_wave = exc_tiles_per_wave(tiles, l);
   a.xcd_run_log2 = enc_xcd_runs(tiles, l) ? kXcdRunLog2 : 0u;
+  // in order, workgroup w of pass 1 holds 8 tiles at B = 4096, those of
+  // workgroups 2w and 2w + 1 of the exception pass: runs of two put these on
+  // w's XCD, whose L2 still holds what they read back (25.2M values: 25.9
+  // against 28.9 us for the encode)
+  a.exc_xcd_run_log2 = a.xcd_run_log2 ? a.xcd_run_log2 : l == 12 ? 1u : 0u;
   return launch_encode(a, stream) == hipSuccess ? CIERA_OK : CIERA_EHIP;
 }
 
@@ -287,8 +294,7 @@ int ciera_hash_blocks(const uint16_t *w, uint64_t n_elems,
   a.w = w;
   a.n = n_elems;
   a.log2B = uint32_t(l);
-  a.num_tiles = uint32_t(enc_tiles(n_elems, uint32_t(l)));
-  a.tile_elems = enc_tile_elems(uint32_t(l));
+  a.num_tiles = uint32_t(enc_tiles(n_elems));
   a.hash_out = hash_cache;
   return launch_hash_blocks(a, stream) == hipSuccess
              ? CIERA_OK

@@ -75,8 +75,7 @@ static_assert((kDecTile & (kDecTile - 1)) == 0 && kDecTile >= 4096,
               "a decode tile holds whole blocks of up to 4096 values");
 
 // Encode: one wave per tile. A tile is one 4096-value chunk (eight octets per
-// lane) when B <= 512, and 8 blocks (8B values, several chunks) when B > 512,
-// so that every tile owns whole bitmap bytes.
+// lane): whole blocks at every B.
 constexpr uint64_t kEncChunk = 4096;
 // B >= 16: the rows (B >= 512) or wave instructions (B < 512) of changed
 // exponents that one wave of the exception pass keeps in flight, and the
@@ -101,12 +100,8 @@ inline uint32_t exc_tiles_per_wave(uint64_t tiles, uint32_t log2B) {
   const uint64_t t = (tiles + waves - 1) / waves;
   return uint32_t(t ? t : 1);
 }
-inline uint64_t enc_tile_elems(uint32_t log2B) {
-  return log2B <= 9 ? kEncChunk : (uint64_t(8) << log2B);
-}
-inline uint64_t enc_tiles(uint64_t n, uint32_t log2B) {
-  const uint64_t T = enc_tile_elems(log2B);
-  const uint64_t t = (n + T - 1) / T;
+inline uint64_t enc_tiles(uint64_t n) {
+  const uint64_t t = (n + kEncChunk - 1) / kEncChunk;
   return t ? t : 1;
 }
 
@@ -117,7 +112,6 @@ struct EncArgs {
   uint64_t n;
   uint32_t log2B;
   uint32_t num_tiles;
-  uint64_t tile_elems;
   uint8_t *out;
   uint64_t *out_bytes;
   WsCtl *ctl;
@@ -127,9 +121,10 @@ struct EncArgs {
   bool scan_prefix;
   // B >= 16: tiles per wave of the exception pass
   uint32_t exc_tiles_per_wave;
-  // pass 1 and the row-wise exception pass: log2 of the workgroups per XCD
-  // turn (0: in order)
+  // log2 of the workgroups per XCD turn in pass 1 and in the row-wise
+  // exception pass (0: in order)
   uint32_t xcd_run_log2;
+  uint32_t exc_xcd_run_log2;
   bool f16;  // fp16 values (B >= 16)
   // block-hash detector (B >= 16) in place of exact compare with `cache`
   bool hashed;
@@ -188,9 +183,12 @@ struct AnsCtl {
 static_assert(sizeof(AnsCtl) == 4096, "rANS control block is 4 KB");
 constexpr int kAnsMinLog2B = 4;  // rANS-coded sections need B >= 16
 inline uint64_t ans_kmax(uint64_t n) { return (n + kAnsChunk - 1) / kAnsChunk; }
-// encode: the control block and a count per tile plus the total
+// encode: the control block and room for a count per tile plus the total, or
+// (B > 512, where no count is kept) per 8 blocks plus one
 inline uint64_t enc_ws_bytes(uint64_t n, uint32_t log2B) {
-  return kWsCtlBytes + 4 * (enc_tiles(n, log2B) + 1);
+  const uint64_t T = log2B <= 9 ? kEncChunk : (uint64_t(8) << log2B);
+  const uint64_t t = (n + T - 1) / T;
+  return kWsCtlBytes + 4 * ((t ? t : 1) + 1);
 }
 // past the control block, the encode counts and the decode tile offsets of
 // nshards shards

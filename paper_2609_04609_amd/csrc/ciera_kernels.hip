@@ -351,29 +351,344 @@ __device__ __forceinline__ uint64_t sm64_mix(uint64_t z) {
 }
 
 // ================================================================ encode ==
-// A tile belongs to one wave (tile id = 4 * workgroup + wave) and holds
-// kEncTile = 4096 values, or 8 blocks when B > 512, so that a tile owns whole
-// bitmap bytes. Lane l handles octets u*64 + l (u = 0..7) of each 4096-value
-// chunk: wave instruction u covers values [512u, 512u + 512) of the chunk.
+// A tile is one chunk of kEncChunk = 4096 values and belongs to one wave. It
+// holds whole blocks at every B (B <= 4096). Lane l handles octets u*64 + l
+// (u = 0..7): wave instruction u covers values [512u, 512u + 512) of it.
 
 // Change detectors of pass 1: exact compare with the exponent cache, or the
 // sender's block hash (HashCache) of Algorithm 1; kDetHashOnly computes the
 // hashes and writes nothing else (seeding HashCache).
 enum : int { kDetExact = 0, kDetHash = 1, kDetHashOnly = 2 };
 
-// Pass 1. Everything but the exception list.
+// Block classes, which fix how a chunk's flags map to bitmap bytes: a block
+// lies inside a 512-value unit (B <= 512), spans 2 or 4 units, or is the
+// whole chunk.
+enum : int { kInUnit = 0, kUnits = 1, kChunkBlock = 2 };
+constexpr int enc_class(uint32_t log2B) {
+  return log2B <= 9 ? kInUnit : log2B < 12 ? kUnits : kChunkBlock;
+}
+
+// The terms of unit u: mix(word XOR state) for both hashes, 0 past n. The
+// lane's octet in unit u is word j of its block: j = lane mod (B/8) when
+// B <= 512, 64 * (u mod (B/512)) + lane above; st0 and st1 are the states of
+// word j mod 64.
+template <bool BIG>
+__device__ __forceinline__ void hash_terms(uint32_t u, uint32_t log2B,
+                                           bool live, uint2 e, uint64_t st0,
+                                           uint64_t st1, uint64_t &ta,
+                                           uint64_t &tb) {
+  const uint64_t word = uint64_t(e.x) | (uint64_t(e.y) << 32);
+  if (BIG) {
+    const uint64_t shift =
+        uint64_t(u & ((1u << (log2B - 9)) - 1u)) * 64 * kSm64Gamma;
+    st0 += shift;
+    st1 += shift;
+  }
+  ta = live ? sm64_mix(word ^ st0) : 0ull;
+  tb = live ? sm64_mix(word ^ st1) : 0ull;
+}
+
+// The order in which a chunk's units are hashed: pairs (i, i + 4), or (2i,
+// 2i + 1) when blocks span units.
+template <bool BIG>
+__device__ constexpr int hash_unit(int q) {
+  return BIG ? q : (q >> 1) + 4 * (q & 1);
+}
+
+// One exchange step over 2H values: each lane hands half of them to its
+// partner across lane bit lbit and keeps the sums of the other half.
+template <int H>
+__device__ __forceinline__ void hash_exchange(uint64_t (&x)[4], uint32_t lane,
+                                              uint32_t lbit) {
+  const bool hi = (lane >> lbit) & 1u;
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const uint64_t sa = hi ? x[i] : x[i + H], ka = hi ? x[i + H] : x[i];
+    x[i] = ka + __shfl_xor(sa, int(1u << lbit), 64);
+  }
+}
+
+// Finish the chunk's block hashes. Summing 8 units (B <= 512: one value per
+// unit) with 8 full reductions would take 48 shuffles a hash; each exchange
+// step hands half of a lane's values to the partner lane across one lane bit
+// and keeps the other half, so 8 values take 4 + 2 + 1 exchanges, and plain
+// xor steps finish the remaining lane bits. The first step, units i and i + 4
+// across lane bit g - 1, is taken as the units are hashed (B > 512: units 2i
+// and 2i + 1 of a block are added), so x and y hold four values here: 64
+// VGPRs and eight waves per SIMD, against 87 and five with all sixteen terms
+// live (OLMoE shard, B = 512: 24.1 against 25.5 us for the hashed encode).
+// With v = log2 of the values a lane holds per chunk (one per unit when
+// B <= 512, one per block above), g = log2 of the lanes sharing a block and
+// t = exchange steps, value i then belongs to local index
+// k = (sel << (v - t)) + i (sel: the lane's bits g-1 .. g-t) and is complete
+// in the lanes whose low g - t bits are 0. Those lanes compare and store the
+// hashes; the change flags go to fw, block c of the chunk in bit c mod 64 of
+// word c / 64.
+template <int DET, bool BIG>
+__device__ __forceinline__ void hash_finish(const EncArgs &a, uint64_t cbase,
+                                            uint32_t lane, uint64_t (&x)[4],
+                                            uint64_t (&y)[4],
+                                            uint64_t (&fw)[4]) {
+  const uint64_t n = a.n;
+  const uint32_t log2B = a.log2B;
+  const uint32_t hv = BIG ? 12u - log2B : 3u;
+  const uint32_t hg = BIG ? 6u : log2B - 3u;
+  const uint32_t ht = hv < hg ? hv : hg;
+  if (BIG) {
+    if (log2B >= 11) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        x[i] = x[2 * i] + x[2 * i + 1];
+        y[i] = y[2 * i] + y[2 * i + 1];
+      }
+    }
+    if (log2B >= 12) {
+      x[0] += x[1];
+      y[0] += y[1];
+    }
+  }
+  // exchange with half size 2^p, p = v-1 .. v-t, across lane bit g-(v-p)
+  if (hv >= 2 && hv - ht <= 1) {
+    hash_exchange<2>(x, lane, hg - (hv - 1u));
+    hash_exchange<2>(y, lane, hg - (hv - 1u));
+  }
+  if (hv >= 1 && hv == ht) {
+    hash_exchange<1>(x, lane, hg - hv);
+    hash_exchange<1>(y, lane, hg - hv);
+  }
+  const uint32_t cnt = 1u << (hv - ht);  // values left per lane
+  for (uint32_t off = (1u << (hg - ht)) >> 1; off > 0; off >>= 1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (uint32_t(i) < cnt) {
+        x[i] += __shfl_xor(x[i], int(off), 64);
+        y[i] += __shfl_xor(y[i], int(off), 64);
+      }
+    }
+  }
+  const bool leader = (lane & ((1u << (hg - ht)) - 1u)) == 0;
+  const uint32_t sel = (lane >> (hg - ht)) & ((1u << ht) - 1u);
+  uint32_t flags = 0;  // bit i: value i's block changed
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (uint32_t(i) >= cnt) continue;
+    const uint32_t k = (sel << (hv - ht)) + uint32_t(i);
+    const uint64_t b_idx =
+        BIG ? (cbase >> log2B) + k
+            : ((cbase + uint64_t(k) * 512) >> log2B) + (lane >> hg);
+    if (leader && (b_idx << log2B) < n) {
+      bool ch = false;
+      if (DET == kDetHash)
+        ch = x[i] != a.hash_in[2 * b_idx] || y[i] != a.hash_in[2 * b_idx + 1];
+      a.hash_out[2 * b_idx] = x[i];
+      a.hash_out[2 * b_idx + 1] = y[i];
+      flags |= uint32_t(ch) << i;
+    }
+  }
+  if (DET == kDetHashOnly) return;
+  if (BIG) {
+    const uint64_t m = __ballot(leader && (flags & 1u));
+    for (uint32_t k = 0; k < (1u << hv); ++k)
+      fw[0] |= ((m >> (k << (6u - ht))) & 1ull) << k;
+  } else {
+    // chunk block c = (k << (6 - g)) + grp; its value sits in lane
+    // (grp << g) + (sel << (g - t)) as value i = k mod cnt
+    const uint32_t nb = kEncChunk >> log2B;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t c = uint32_t(q) * 64u + lane;
+      const uint32_t k = c >> (6u - hg);
+      const uint32_t grp = c & ((1u << (6u - hg)) - 1u);
+      const uint32_t src =
+          ((grp << hg) + ((k >> (hv - ht)) << (hg - ht))) & 63u;
+      const uint32_t fl = __shfl(flags, int(src), 64);
+      fw[q] = __ballot(c < nb && ((fl >> (k & (cnt - 1u))) & 1u));
+    }
+  }
+}
+
+// One chunk of pass 1: everything but the exception list and the bitmap. The
+// lane's exponents go to e, its octets' change bits to mask (B = 1: a bit per
+// value; exact compare: nonzero where an octet differs) and the chunk's block
+// flags (B >= 16) to fw, block c in bit c mod 64 of word c / 64.
 // NTW (the fused cache update): the exception pass takes the changed
 // exponents from the cache brought forward here, so W' is read once and its
 // loads are non-temporal, while the cache bytes are loaded plainly for the
 // exception pass to find again. Without it the exception pass re-reads W'
 // and the cache is read once: the other way round.
-template <bool ELEMS, int DET, bool F16 = false, bool NTW = false>
-__global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
+template <bool ELEMS, int DET, bool F16, bool NTW, bool BIG>
+__device__ __forceinline__ void encode_chunk(const EncArgs &a, uint64_t cbase,
+                                             uint32_t lane, uint8_t *sm_out,
+                                             uint2 (&e)[8],
+                                             uint32_t (&mask)[8],
+                                             uint64_t (&fw)[4]) {
   constexpr bool HASH = DET != kDetExact;
   constexpr bool OUT = DET != kDetHashOnly;
   static_assert(!(HASH && ELEMS), "the block hash needs B >= 16");
   static_assert(!(F16 && (HASH || ELEMS)), "fp16: exact compare, B >= 16");
-  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t n = a.n;
+  const uint32_t log2B = a.log2B;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) fw[k] = 0ull;
+  // block hash: the states of the lane's words, and the sums of the units
+  // hashed so far (see hash_finish)
+  uint64_t st0 = 0, st1 = 0, hx[4], hy[4];
+  uint32_t hbit = 0;
+  if (HASH) {
+    const uint64_t j =
+        BIG ? lane : uint64_t(lane & ((1u << (log2B - 3)) - 1u));
+    st0 = kHashSeed0 + (j + 1) * kSm64Gamma;
+    st1 = kHashSeed1 + (j + 1) * kSm64Gamma;
+    hbit = BIG ? 0u : log2B - 4u;
+  }
+  // hash units ua and ub (their octets' exponents known) into value i
+  auto hash_pair = [&](int i, uint32_t ua, uint32_t ub, bool la, bool lb) {
+    uint64_t xs[4], ys[4];
+    hash_terms<BIG>(ua, log2B, la, e[ua], st0, st1, xs[0], ys[0]);
+    hash_terms<BIG>(ub, log2B, lb, e[ub], st0, st1, xs[1], ys[1]);
+    if (BIG) {
+      hx[i] = xs[0] + xs[1];
+      hy[i] = ys[0] + ys[1];
+    } else {
+      hash_exchange<1>(xs, lane, hbit);
+      hash_exchange<1>(ys, lane, hbit);
+      hx[i] = xs[0];
+      hy[i] = ys[0];
+    }
+  };
+  // the octet's exponents and sign|mantissa bytes from its values
+  auto split = [&](uint4 wv, uint64_t elem, uint2 &ev, uint2 &sm) {
+    if (F16) {
+      uint2 hi;
+      split4_f16(wv.x, wv.y, ev.x, sm.x, hi.x);
+      split4_f16(wv.z, wv.w, ev.y, sm.y, hi.y);
+      uint8_t *pl = sm_out + n + 3 * (elem >> 3);
+#pragma unroll
+      for (uint32_t q = 0; q < 3; ++q)
+        pl[q] = uint8_t(plane_byte(hi.x, hi.y, q));
+    } else {
+      split4(wv.x, wv.y, ev.x, sm.x);
+      split4(wv.z, wv.w, ev.y, sm.y);
+    }
+  };
+  auto compare = [&](uint2 ev, uint2 cv) {
+    return ELEMS ? (bytes_ne4(ev.x, cv.x) | (bytes_ne4(ev.y, cv.y) << 4))
+                 : uint32_t((ev.x != cv.x) || (ev.y != cv.y));
+  };
+  if (cbase + kEncChunk <= n) {
+    uint4 wv[8];
+    uint2 cv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      wv[u] = NTW ? ld_nt16(a.w + cbase + (uint64_t(u) * 64 + lane) * 8)
+                  : ld16(a.w + cbase + (uint64_t(u) * 64 + lane) * 8);
+    if (!HASH) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        cv[u] = NTW ? ld8(a.cache + cbase + (uint64_t(u) * 64 + lane) * 8)
+                    : ld_nt8(a.cache + cbase + (uint64_t(u) * 64 + lane) * 8);
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int u = HASH ? hash_unit<BIG>(q) : q;
+      const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
+      uint2 sm;
+      split(wv[u], elem, e[u], sm);
+      if (OUT) st_nt8(sm_out + elem, sm);
+      if (HASH) {
+        mask[u] = 0;
+        if (q & 1)
+          hash_pair(q >> 1, uint32_t(hash_unit<BIG>(q - 1)), uint32_t(u),
+                    true, true);
+      } else {
+        mask[u] = compare(e[u], cv[u]);
+        // the sender's cache brought forward: only octets that differ
+        if (a.cache_out && mask[u]) st8(a.cache_out + elem, e[u]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
+      const uint32_t valid = octet_valid(elem, n);
+      mask[u] = 0;
+      e[u] = make_uint2(0u, 0u);
+      if (valid) {
+        // load_w8 zero-fills past n: those fields are 0 in the planes and
+        // the hash words, and never a change against a cached 0
+        uint2 sm;
+        split(load_w8(a.w + elem, valid), elem, e[u], sm);
+        if (OUT) store_b8(sm_out + elem, sm, valid);
+        if (!HASH) {
+          mask[u] = compare(e[u], load_b8(a.cache + elem, valid));
+          if (a.cache_out && mask[u])
+            store_b8(a.cache_out + elem, e[u], valid);
+        }
+      }
+    }
+    if (HASH) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t ua = uint32_t(hash_unit<BIG>(2 * i)),
+                       ub = uint32_t(hash_unit<BIG>(2 * i + 1));
+        hash_pair(i, ua, ub, cbase + (uint64_t(ua) * 64 + lane) * 8 < n,
+                  cbase + (uint64_t(ub) * 64 + lane) * 8 < n);
+      }
+    }
+  }
+  if (HASH) {
+    hash_finish<DET, BIG>(a, cbase, lane, hx, hy, fw);
+  } else if (!ELEMS) {
+    uint64_t m[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m[u] = __ballot(mask[u] != 0);
+    if (!BIG) {
+      // 512/B blocks per 512-value unit, B/8 octets (bits of m[u]) each
+      const uint32_t opb_log2 = log2B - 3;
+      const uint32_t bpu_log2 = 6 - opb_log2;
+      const uint64_t gmask =
+          opb_log2 == 6 ? ~0ull : ((1ull << (1u << opb_log2)) - 1ull);
+      const uint32_t nb = kEncChunk >> log2B;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t b = uint32_t(k) * 64u + lane;
+        bool f = false;
+        if (b < nb) {
+          const uint64_t word = pick<8>(m, b >> bpu_log2);
+          const uint32_t sh = (b & ((1u << bpu_log2) - 1u)) << opb_log2;
+          f = ((word >> sh) & gmask) != 0;
+        }
+        fw[k] = __ballot(f);
+      }
+    } else {
+      // a block spans 2^(log2B-9) units
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (m[u]) fw[0] |= 1ull << (uint32_t(u) >> (log2B - 9));
+    }
+  }
+}
+
+// Pass 1 for blocks of class CLS. A bitmap byte holds 8 blocks. Up to B = 512
+// a chunk fills whole bytes; above, 2, 4 or 8 chunks share one, so the
+// workgroup's waves put their bits together in LDS: at B = 4096 that takes 8
+// waves (elsewhere 4, which keeps the tiles of a workgroup and of the
+// exception pass's workgroup alike).
+// Bound by HBM (4 bytes a value). A wave that went on over 8 blocks, as it did
+// above B = 512, left 768 waves on the chip at B = 4096 and 25.2M values; with
+// a chunk a wave the encode of that shard (both passes) takes 25.9 instead of
+// 42.4 us, of 88.1M clustered values 84.7 instead of 92.5 us, of 4.0M values
+// 11.4 instead of 36.4 us. Without the loop over chunks the kernel also
+// needs 62 instead of 78 VGPRs (eight waves per SIMD); at B = 512 the OLMoE
+// shard's encode takes 23.2 instead of 23.4 us.
+constexpr int enc_waves(int cls) { return cls == kChunkBlock ? 8 : 4; }
+template <bool ELEMS, int DET, bool F16, bool NTW, int CLS>
+__global__ __launch_bounds__(64 * enc_waves(CLS)) void encode_pass_kernel(
+    EncArgs a) {
+  constexpr bool OUT = DET != kDetHashOnly;
+  constexpr int W = enc_waves(CLS);
+  __shared__ uint32_t s_bits[W];
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // Workgroup L = 8k + x runs on XCD x as its k-th. With runs of
   // G = 2^a.xcd_run_log2 workgroups it takes the tiles of workgroup
   // (k / G) 8G + x G + k mod G, so each XCD streams G neighbouring
@@ -386,12 +701,13 @@ __global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
       grp = ((k >> g) << (g + 3)) | ((grp & 7u) << g) | (k & ((1u << g) - 1u));
     }
   }
-  const uint32_t tile = grp * 4u + (threadIdx.x >> 6);
-  if (tile >= a.num_tiles) return;
-  const uint64_t n = a.n;
+  const uint32_t tile = grp * uint32_t(W) + wave;
   const uint32_t log2B = a.log2B;
-  const uint64_t T = a.tile_elems;
-  const uint64_t tbase = uint64_t(tile) * T;
+  constexpr bool shared_bytes = OUT && !ELEMS && CLS != kInUnit;
+  const bool live = tile < a.num_tiles;
+  if (!live && !shared_bytes) return;
+  const uint64_t n = a.n;
+  const uint64_t cbase = uint64_t(tile) * kEncChunk;
   const uint64_t S_sm = sm_bytes(n, F16);  // sign+mantissa section
   const uint64_t n16 = pad16(S_sm);
   const uint64_t bm = bitmap_bytes(n, log2B);
@@ -399,277 +715,25 @@ __global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
   uint8_t *const sm_out = OUT ? a.out + kHeaderBytes : nullptr;
   uint8_t *const bmp_out = OUT ? sm_out + n16 : nullptr;
 
-  uint32_t count = 0;
-  uint64_t fw[4] = {0ull, 0ull, 0ull, 0ull};  // block flags, B <= 512
-  uint32_t fbyte = 0;                          // block flags, B > 512
-
-  // Block hash. The lane's octet in unit u is word j of its block: j = lane
-  // mod (B/8) when B <= 512, 64 * (u mod (B/512)) + lane above.
-  uint64_t st0 = 0, st1 = 0;
-  // Sums over a block: v = log2 of the values each lane holds per chunk (one
-  // per unit when B <= 512, one per block above), g = log2 of the lanes
-  // sharing a block, t = exchange steps (see hash_chunk).
-  uint32_t hv = 0, hg = 0, ht = 0;
-  if (HASH) {
-    const uint64_t j =
-        log2B <= 9 ? uint64_t(lane & ((1u << (log2B - 3)) - 1u)) : lane;
-    st0 = kHashSeed0 + (j + 1) * kSm64Gamma;
-    st1 = kHashSeed1 + (j + 1) * kSm64Gamma;
-    hv = log2B <= 9 ? 3u : 12u - log2B;
-    hg = log2B <= 9 ? log2B - 3u : 6u;
-    ht = hv < hg ? hv : hg;
-  }
-  // The terms of unit u: mix(word XOR state) for both hashes, 0 past n.
-  auto hash_terms = [&](uint32_t u, uint64_t cbase, uint64_t word,
-                        uint64_t &ta, uint64_t &tb) {
-    const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
-    uint64_t s0 = st0, s1 = st1;
-    if (log2B > 9) {
-      const uint64_t shift =
-          uint64_t(u & ((1u << (log2B - 9)) - 1u)) * 64 * kSm64Gamma;
-      s0 += shift;
-      s1 += shift;
-    }
-    ta = elem < n ? sm64_mix(word ^ s0) : 0ull;
-    tb = elem < n ? sm64_mix(word ^ s1) : 0ull;
-  };
-  // Finish the chunk's block hashes from the per-unit terms: fold units into
-  // blocks (B > 512), then sum over the lanes of each block. Each exchange
-  // step hands half of the lane's values to the partner lane across one lane
-  // bit and keeps the other half, so 8 values take 4 + 2 + 1 exchanges
-  // instead of 8 full reductions; plain xor steps finish the remaining lane
-  // bits. Value i then belongs to local index k = (sel << (v - t)) + i (sel:
-  // the lane's bits g-1 .. g-t) and is complete in the lanes whose low g - t
-  // bits are 0. Those lanes compare and store the hashes; the change flags go
-  // to fw (B <= 512) or fbyte.
-  auto hash_chunk = [&](uint64_t cbase, uint64_t (&x)[8], uint64_t (&y)[8]) {
-    if (log2B > 9) {
-      const uint32_t ul = log2B - 9;
-      if (ul >= 1) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          x[i] = x[2 * i] + x[2 * i + 1];
-          y[i] = y[2 * i] + y[2 * i + 1];
-        }
-      }
-      if (ul >= 2) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          x[i] = x[2 * i] + x[2 * i + 1];
-          y[i] = y[2 * i] + y[2 * i + 1];
-        }
-      }
-      if (ul >= 3) {
-        x[0] += x[1];
-        y[0] += y[1];
-      }
-    }
-    // exchange with half size 2^p, p = v-1 .. v-t, across lane bit g-(v-p)
-    auto exchange = [&](auto hc, uint32_t lbit) {
-      constexpr int H = decltype(hc)::value;
-      const bool hi = (lane >> lbit) & 1u;
-      const int off = int(1u << lbit);
-#pragma unroll
-      for (int i = 0; i < H; ++i) {
-        const uint64_t sa = hi ? x[i] : x[i + H], ka = hi ? x[i + H] : x[i];
-        const uint64_t sb = hi ? y[i] : y[i + H], kb = hi ? y[i + H] : y[i];
-        x[i] = ka + __shfl_xor(sa, off, 64);
-        y[i] = kb + __shfl_xor(sb, off, 64);
-      }
-    };
-    if (hv >= 3 && hv - ht <= 2)
-      exchange(std::integral_constant<int, 4>{}, hg - 1u);
-    if (hv >= 2 && hv - ht <= 1)
-      exchange(std::integral_constant<int, 2>{}, hg - (hv - 1u));
-    if (hv >= 1 && hv == ht)
-      exchange(std::integral_constant<int, 1>{}, hg - hv);
-    const uint32_t cnt = 1u << (hv - ht);  // values left per lane
-    for (uint32_t off = (1u << (hg - ht)) >> 1; off > 0; off >>= 1) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (uint32_t(i) < cnt) {
-          x[i] += __shfl_xor(x[i], int(off), 64);
-          y[i] += __shfl_xor(y[i], int(off), 64);
-        }
-      }
-    }
-    const bool leader = (lane & ((1u << (hg - ht)) - 1u)) == 0;
-    const uint32_t sel =
-        (lane >> (hg - ht)) & ((1u << ht) - 1u);
-    uint32_t flags = 0;  // bit i: value i's block changed
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (uint32_t(i) >= cnt) continue;
-      const uint32_t k = (sel << (hv - ht)) + uint32_t(i);
-      const uint64_t b_idx = log2B <= 9
-                                 ? ((cbase + uint64_t(k) * 512) >> log2B) +
-                                       (lane >> hg)
-                                 : (cbase >> log2B) + k;
-      if (leader && (b_idx << log2B) < n) {
-        bool ch = false;
-        if (DET == kDetHash)
-          ch = x[i] != a.hash_in[2 * b_idx] || y[i] != a.hash_in[2 * b_idx + 1];
-        a.hash_out[2 * b_idx] = x[i];
-        a.hash_out[2 * b_idx + 1] = y[i];
-        flags |= uint32_t(ch) << i;
-      }
-    }
-    if (!OUT) return;
-    if (log2B <= 9) {
-      // chunk block c = (k << (6 - g)) + grp; its value sits in lane
-      // (grp << g) + (sel << (g - t)) as value i = k mod cnt
-      const uint32_t nb = kEncChunk >> log2B;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t c = uint32_t(q) * 64u + lane;
-        const uint32_t k = c >> (6u - hg);
-        const uint32_t grp = c & ((1u << (6u - hg)) - 1u);
-        const uint32_t src =
-            ((grp << hg) + ((k >> (hv - ht)) << (hg - ht))) & 63u;
-        const uint32_t fl = __shfl(flags, int(src), 64);
-        fw[q] = __ballot(c < nb && ((fl >> (k & (cnt - 1u))) & 1u));
-      }
-    } else {
-      const uint64_t m = __ballot(leader && (flags & 1u));
-      const uint32_t cb0 = uint32_t((cbase - tbase) >> log2B);
-      for (uint32_t k = 0; k < (1u << hv); ++k)
-        if ((m >> (k << (6u - ht))) & 1ull) fbyte |= 1u << (cb0 + k);
-    }
-  };
-
-  for (uint64_t cbase = tbase; cbase < tbase + T; cbase += kEncChunk) {
-    uint32_t mask[8];  // change bits of the lane's octets
-    uint64_t ta[8], tb[8];  // block-hash terms of the lane's octets
-    if (cbase + kEncChunk <= n) {
-      uint4 wv[8];
-      uint2 cv[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        wv[u] = NTW ? ld_nt16(a.w + cbase + (uint64_t(u) * 64 + lane) * 8)
-                    : ld16(a.w + cbase + (uint64_t(u) * 64 + lane) * 8);
-      if (!HASH) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          cv[u] = NTW ? ld8(a.cache + cbase + (uint64_t(u) * 64 + lane) * 8)
-                      : ld_nt8(a.cache + cbase + (uint64_t(u) * 64 + lane) * 8);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
-        uint2 e, sm;
-        if (F16) {
-          uint2 hi;
-          split4_f16(wv[u].x, wv[u].y, e.x, sm.x, hi.x);
-          split4_f16(wv[u].z, wv[u].w, e.y, sm.y, hi.y);
-          uint8_t *pl = sm_out + n + 3 * (elem >> 3);
-#pragma unroll
-          for (uint32_t q = 0; q < 3; ++q)
-            pl[q] = uint8_t(plane_byte(hi.x, hi.y, q));
-        } else {
-          split4(wv[u].x, wv[u].y, e.x, sm.x);
-          split4(wv[u].z, wv[u].w, e.y, sm.y);
-        }
-        if (OUT) st_nt8(sm_out + elem, sm);
-        if (HASH) {
-          hash_terms(uint32_t(u), cbase,
-                     uint64_t(e.x) | (uint64_t(e.y) << 32), ta[u], tb[u]);
-          mask[u] = 0;
-        } else {
-          mask[u] = ELEMS ? (bytes_ne4(e.x, cv[u].x) |
-                             (bytes_ne4(e.y, cv[u].y) << 4))
-                          : uint32_t((e.x != cv[u].x) || (e.y != cv[u].y));
-          // the sender's cache brought forward: only octets that differ
-          if (a.cache_out && mask[u]) st8(a.cache_out + elem, e);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
-        const uint32_t valid = octet_valid(elem, n);
-        mask[u] = 0;
-        uint64_t word = 0;
-        if (valid) {
-          const uint4 wv = load_w8(a.w + elem, valid);
-          uint2 e, sm;
-          if (F16) {
-            // load_w8 zero-fills past n: those fields are 0 in the planes
-            uint2 hi;
-            split4_f16(wv.x, wv.y, e.x, sm.x, hi.x);
-            split4_f16(wv.z, wv.w, e.y, sm.y, hi.y);
-            uint8_t *pl = sm_out + n + 3 * (elem >> 3);
-#pragma unroll
-            for (uint32_t q = 0; q < 3; ++q)
-              pl[q] = uint8_t(plane_byte(hi.x, hi.y, q));
-          } else {
-            split4(wv.x, wv.y, e.x, sm.x);
-            split4(wv.z, wv.w, e.y, sm.y);
-          }
-          if (OUT) store_b8(sm_out + elem, sm, valid);
-          if (HASH) {
-            // load_w8 zero-fills past n: those bytes are 0 in the word
-            word = uint64_t(e.x) | (uint64_t(e.y) << 32);
-          } else {
-            const uint2 cv = load_b8(a.cache + elem, valid);
-            // padding values are 0 with a cached 0: never a change
-            mask[u] = ELEMS ? (bytes_ne4(e.x, cv.x) |
-                               (bytes_ne4(e.y, cv.y) << 4))
-                            : uint32_t((e.x != cv.x) || (e.y != cv.y));
-            if (a.cache_out && mask[u])
-              store_b8(a.cache_out + elem, e, valid);
-          }
-        }
-        if (HASH) hash_terms(uint32_t(u), cbase, word, ta[u], tb[u]);
-      }
-    }
-    if (HASH) hash_chunk(cbase, ta, tb);
-    if (!OUT) continue;
-    if (ELEMS) {
-      // an octet's change byte is its bitmap byte
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
-        if (elem < n) bmp_out[elem >> 3] = uint8_t(mask[u]);
-        count += __popc(mask[u]);
-      }
-    } else {
-      uint64_t m[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) m[u] = HASH ? 0ull : __ballot(mask[u] != 0);
-      if (HASH) {
-        // hash_chunk has set the flags
-      } else if (log2B <= 9) {
-        // 512/B blocks per 512-value unit, B/8 octets (bits of m[u]) each
-        const uint32_t opb_log2 = log2B - 3;
-        const uint32_t bpu_log2 = 6 - opb_log2;
-        const uint64_t gmask =
-            opb_log2 == 6 ? ~0ull : ((1ull << (1u << opb_log2)) - 1ull);
-        const uint32_t nb = kEncChunk >> log2B;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t b = uint32_t(k) * 64u + lane;
-          bool f = false;
-          if (b < nb) {
-            const uint64_t word = pick<8>(m, b >> bpu_log2);
-            const uint32_t sh = (b & ((1u << bpu_log2) - 1u)) << opb_log2;
-            f = ((word >> sh) & gmask) != 0;
-          }
-          fw[k] = __ballot(f);
-        }
-      } else {
-        // a block spans 2^(log2B-9) units; the tile holds 8 blocks
-        const uint32_t u0 = uint32_t((cbase - tbase) >> 9);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (m[u]) fbyte |= 1u << ((u0 + uint32_t(u)) >> (log2B - 9));
-      }
-    }
-  }
+  uint32_t mask[8];
+  uint2 e[8];
+  uint64_t fw[4];
+  if (live)
+    encode_chunk<ELEMS, DET, F16, NTW, CLS != kInUnit>(a, cbase, lane, sm_out,
+                                                       e, mask, fw);
   if (!OUT) return;
 
+  uint32_t count = 0;
   if (ELEMS) {
+    // an octet's change byte is its bitmap byte
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
+      if (elem < n) bmp_out[elem >> 3] = uint8_t(mask[u]);
+      count += __popc(mask[u]);
+    }
     count = wave_sum(count);
-  } else if (log2B <= 9) {
+  } else if (CLS == kInUnit) {
     const uint32_t nbytes = uint32_t(kEncChunk >> log2B) >> 3;
     const uint64_t byte0 = uint64_t(tile) * nbytes;
     for (uint32_t i = lane; i < nbytes; i += 64) {
@@ -680,8 +744,18 @@ __global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) count += uint32_t(__popcll(fw[k]));
   } else {
-    if (lane == 0 && tile < bm16) bmp_out[tile] = uint8_t(fbyte);
-    count = __popc(fbyte);
+    const uint32_t nb_log2 = 12 - log2B;  // log2 of the blocks in a chunk
+    const uint32_t cpb = 1u << (log2B - 9);  // chunks per bitmap byte
+    if (lane == 0) s_bits[wave] = live ? uint32_t(fw[0]) : 0u;
+    __syncthreads();
+    if (!live) return;
+    const uint64_t pos = uint64_t(tile) >> (log2B - 9);
+    if (lane == 0 && (wave & (cpb - 1u)) == 0 && pos < bm16) {
+      uint32_t b = 0;
+      for (uint32_t i = 0; i < cpb && wave + i < uint32_t(W); ++i)
+        b |= s_bits[wave + i] << (i << nb_log2);
+      bmp_out[pos] = uint8_t(b);
+    }
   }
   if ((ELEMS || a.scan_prefix) && lane == 0) a.counts[tile] = count;
 
@@ -691,8 +765,7 @@ __global__ __launch_bounds__(kThreads) void encode_pass_kernel(EncArgs a) {
     for (uint64_t i = S_sm + lane; i < n16; i += 64) sm_out[i] = 0;
     uint64_t written = bm;
     if (!ELEMS)
-      written = log2B <= 9 ? uint64_t(a.num_tiles) * ((kEncChunk >> log2B) >> 3)
-                           : uint64_t(a.num_tiles);
+      written = ((uint64_t(a.num_tiles) << (12 - log2B)) + 7) >> 3;
     if (written > bm16) written = bm16;
     for (uint64_t i = written + lane; i < bm16; i += 64) bmp_out[i] = 0;
   }
@@ -929,7 +1002,7 @@ __global__ __launch_bounds__(kThreads) void encode_exc_elems_kernel(
   const uint32_t tile = blockIdx.x * 4u + wave;
   const bool live = tile < nt;  // every wave takes part in the count
   const uint64_t n = a.n;
-  const uint64_t tbase = uint64_t(tile) * a.tile_elems;
+  const uint64_t tbase = uint64_t(tile) * kEncChunk;
   const uint64_t n16 = pad16(sm_bytes(n, false));
   const uint8_t *const bmp = a.out + kHeaderBytes + n16;
   uint8_t *const exc_out =
@@ -985,11 +1058,11 @@ __global__ __launch_bounds__(kThreads) void encode_exc_elems_kernel(
 // Pass 2 for B >= 512. A row of 512 values lies inside one block, so it is
 // changed or unchanged as a whole, and the exceptions of the changed rows
 // follow one another in row order: the k-th changed row's exponents start at
-// 512 k in the list. A tile (8 blocks) is one bitmap byte. Each wave takes a
-// run of a.exc_tiles_per_wave tiles and copies its changed rows D at a time,
-// so that that many reads of the rows' exponents are in flight per wave; the
-// first batch is issued before the offset of the run (the changed blocks in
-// front of it) is counted, and the two overlap.
+// 512 k in the list. A tile is 8 rows (4096 values, whole blocks). Each wave
+// takes a run of a.exc_tiles_per_wave tiles and copies its changed rows D at a
+// time, so that that many reads of the rows' exponents are in flight per wave;
+// the first batch is issued before the offset of the run (the changed blocks
+// in front of it) is counted, and the two overlap.
 template <bool F16, bool FROMC, uint32_t D>
 __global__ __launch_bounds__(kThreads) void encode_exc_rows_kernel(EncArgs a) {
   using Src = ExcSrc<F16, FROMC>;
@@ -1003,10 +1076,10 @@ __global__ __launch_bounds__(kThreads) void encode_exc_rows_kernel(EncArgs a) {
   const uint8_t *const bmp = a.out + kHeaderBytes + n16;
   uint8_t *const exc_out = a.out + kHeaderBytes + n16 + pad16(bm);
   const uint64_t nt = a.num_tiles, tpw = a.exc_tiles_per_wave;
-  // the workgroups in runs per XCD where pass 1 takes them (as there)
+  // the workgroups in runs per XCD (as in pass 1)
   uint32_t grp = blockIdx.x;
-  if (a.xcd_run_log2) {
-    const uint32_t g = a.xcd_run_log2;
+  if (a.exc_xcd_run_log2) {
+    const uint32_t g = a.exc_xcd_run_log2;
     if (grp < ((gridDim.x >> (g + 3)) << (g + 3))) {
       const uint32_t k = grp >> 3;
       grp = ((k >> g) << (g + 3)) | ((grp & 7u) << g) | (k & ((1u << g) - 1u));
@@ -1016,8 +1089,8 @@ __global__ __launch_bounds__(kThreads) void encode_exc_rows_kernel(EncArgs a) {
   const uint64_t t0 = min(g0 + wave * tpw, nt);
   const uint64_t t1 = min(t0 + tpw, nt);
   const uint64_t rows = (n + 511) >> 9;
-  const uint64_t r0 = min(t0 << (rpb_log2 + 3), rows);
-  const uint64_t r1 = min(t1 << (rpb_log2 + 3), rows);
+  const uint64_t r0 = min(t0 << 3, rows);
+  const uint64_t r1 = min(t1 << 3, rows);
 
   // changed rows among [c, c + 64) of the run, as a wave-uniform mask
   auto chunk_mask = [&](uint64_t c) -> uint64_t {
@@ -1059,14 +1132,20 @@ __global__ __launch_bounds__(kThreads) void encode_exc_rows_kernel(EncArgs a) {
   if (a.scan_prefix) {
     prefix = a.counts[t0];
   } else {
-    const uint64_t gb = min(g0, bm);  // the workgroup's bytes in front
-    const uint64_t sb = min(t0, bm);  // + the sibling runs in front
+    const uint64_t gb = (g0 << 3) >> (rpb_log2 + 3);  // whole bytes in front
+    const uint64_t b0 = (t0 << 3) >> rpb_log2;  // the run's first block
+    // bits of byte i in front of b0 (the sibling runs' and the byte they end
+    // in): whole bytes, then a partial one
+    auto front = [&](uint64_t i, uint32_t v) {
+      const uint64_t left = b0 > (i << 3) ? b0 - (i << 3) : 0;
+      return uint32_t(__popc(left < 8 ? v & ((1u << left) - 1u) : v));
+    };
     const uint64_t si = gb + lane;
     const uint32_t sv = bm ? bmp[min(si, bm - 1)] : 0u;
-    const uint32_t cg = popc_bytes_part<kGroupLoads>(bmp, gb);
-    uint32_t cs = si < sb ? uint32_t(__popc(sv)) : 0u;
-    for (uint64_t i = si + 64; i < sb; i += 64)  // runs of > 21 tiles
-      cs += __popc(uint32_t(bmp[i]));
+    const uint32_t cg = popc_bytes_part<kGroupLoads>(bmp, min(gb, bm));
+    uint32_t cs = si < bm ? front(si, sv) : 0u;
+    for (uint64_t i = si + 64; i < min((b0 + 7) >> 3, bm); i += 64)
+      cs += front(i, bmp[i]);  // runs of > 21 tiles
     prefix = block_sum(cg, s_red) + wave_sum(cs);
   }
 
@@ -1094,8 +1173,11 @@ __global__ __launch_bounds__(kThreads) void encode_exc_rows_kernel(EncArgs a) {
 
   if (t0 < nt && t1 == nt) {
     uint32_t own = 0;
-    for (uint64_t i = t0 + lane; i < min(t1, bm); i += 64)
-      own += __popc(uint32_t(bmp[i]));
+    const uint64_t b0 = (t0 << 3) >> rpb_log2;
+    for (uint64_t i = (b0 >> 3) + lane; i < bm; i += 64) {
+      const uint32_t skip = i == (b0 >> 3) ? uint32_t(b0 & 7u) : 0u;
+      own += __popc(uint32_t(bmp[i]) >> skip);
+    }
     exc_finish<false, F16>(a, uint64_t(prefix) + wave_sum(own), lane);
   }
 }
@@ -1867,6 +1949,18 @@ __global__ void fill_zero_kernel(uint32_t *p, uint64_t words) {
 namespace {
 template <bool B>
 using bool_c = std::integral_constant<bool, B>;
+template <int I>
+using int_c = std::integral_constant<int, I>;
+
+// go(class of the block size), as a template argument
+template <typename Go>
+void by_class(uint32_t log2B, Go go) {
+  switch (enc_class(log2B)) {
+    case kInUnit: go(int_c<kInUnit>{}); break;
+    case kUnits: go(int_c<kUnits>{}); break;
+    default: go(int_c<kChunkBlock>{}); break;
+  }
+}
 
 // Launch the exception-pass kernel that pick(f16, from_cache) names, with the
 // two flags as template arguments (f16 is always false at B = 1).
@@ -1885,26 +1979,34 @@ void launch_exc(dim3 grid, const EncArgs &a, bool f16, bool fromc,
 }  // namespace
 
 hipError_t launch_encode(const EncArgs &a, hipStream_t s) {
-  const dim3 grid((a.num_tiles + 3) / 4), block(kThreads);
+  const dim3 grid((a.num_tiles + 3) / 4);
   const bool elems = a.log2B == 0;
   // with the fused cache update the exception pass reads the cache, not W'
   const bool fromc = a.cache_out != nullptr;
+  auto pass = [&](auto e, auto det, auto f, auto c) {
+    constexpr bool E = decltype(e)::value, F = decltype(f)::value,
+                   C = decltype(c)::value;
+    constexpr int D = decltype(det)::value;
+    auto go = [&](auto cls) {
+      constexpr int K = E ? int(kInUnit) : decltype(cls)::value;
+      constexpr uint32_t W = enc_waves(K);
+      hipLaunchKernelGGL((encode_pass_kernel<E, D, F, C, K>),
+                         dim3((a.num_tiles + W - 1) / W), dim3(64 * W), 0, s,
+                         a);
+    };
+    by_class(a.log2B, go);
+  };
   auto exact = [&](auto e, auto f) {
-    constexpr bool E = decltype(e)::value, F = decltype(f)::value;
-    if (fromc)
-      hipLaunchKernelGGL((encode_pass_kernel<E, kDetExact, F, true>), grid,
-                         block, 0, s, a);
-    else
-      hipLaunchKernelGGL((encode_pass_kernel<E, kDetExact, F, false>), grid,
-                         block, 0, s, a);
+    constexpr int_c<kDetExact> det{};
+    if (fromc) pass(e, det, f, bool_c<true>{});
+    else pass(e, det, f, bool_c<false>{});
   };
   if (elems)
     exact(bool_c<true>{}, bool_c<false>{});
   else if (a.f16)
     exact(bool_c<false>{}, bool_c<true>{});
   else if (a.hashed)
-    hipLaunchKernelGGL((encode_pass_kernel<false, kDetHash>), grid, block, 0,
-                       s, a);
+    pass(bool_c<false>{}, int_c<kDetHash>{}, bool_c<false>{}, bool_c<false>{});
   else
     exact(bool_c<false>{}, bool_c<false>{});
   if (a.scan_prefix)
@@ -1941,8 +2043,13 @@ hipError_t launch_encode(const EncArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_hash_blocks(const EncArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL((encode_pass_kernel<false, kDetHashOnly>),
-                     dim3((a.num_tiles + 3) / 4), dim3(kThreads), 0, s, a);
+  by_class(a.log2B, [&](auto cls) {
+    constexpr int K = decltype(cls)::value;
+    constexpr uint32_t W = enc_waves(K);
+    hipLaunchKernelGGL((encode_pass_kernel<false, kDetHashOnly, false, false,
+                                           K>),
+                       dim3((a.num_tiles + W - 1) / W), dim3(64 * W), 0, s, a);
+  });
   return hipGetLastError();
 }
 
