@@ -77,6 +77,15 @@ static_assert((kDecTile & (kDecTile - 1)) == 0 && kDecTile >= 4096,
 // Encode: one wave per tile. A tile is one 4096-value chunk (eight octets per
 // lane): whole blocks at every B.
 constexpr uint64_t kEncChunk = 4096;
+// Shards of up to this many values are encoded by one workgroup in one launch
+// (encode_small_kernel): 12 of its 16 waves' chunks. One CU needs 4.2 us for
+// 128 values, 5.9 for 32,768 and 8.1 for 65,536, the two launches 5.4, 7.0 and
+// 7.0 (encodes back to back in a HIP graph, B = 512); with the block hash or in
+// fp16 a full round takes 9 to 10 us, and the lines cross at the same place.
+#ifndef CIERA_ENC_SMALL
+#define CIERA_ENC_SMALL 49152
+#endif
+constexpr uint64_t kEncSmall = CIERA_ENC_SMALL;
 // B >= 16: the rows (B >= 512) or wave instructions (B < 512) of changed
 // exponents that one wave of the exception pass keeps in flight, and the
 // number of waves it aims for (each wave takes a run of exc_tiles_per_wave

@@ -669,6 +669,21 @@ __device__ __forceinline__ void encode_chunk(const EncArgs &a, uint64_t cbase,
   }
 }
 
+// The padding of the first two sections, and the bitmap bytes that no chunk
+// holds, zeroed by one wave.
+template <bool ELEMS, bool F16>
+__device__ __forceinline__ void pad_sections(const EncArgs &a, uint32_t lane) {
+  const uint64_t S_sm = sm_bytes(a.n, F16), n16 = pad16(S_sm);
+  const uint64_t bm = bitmap_bytes(a.n, a.log2B), bm16 = pad16(bm);
+  uint8_t *const sm_out = a.out + kHeaderBytes;
+  for (uint64_t i = S_sm + lane; i < n16; i += 64) sm_out[i] = 0;
+  uint64_t written = bm;
+  if (!ELEMS)
+    written = ((uint64_t(a.num_tiles) << (12 - a.log2B)) + 7) >> 3;
+  if (written > bm16) written = bm16;
+  for (uint64_t i = written + lane; i < bm16; i += 64) sm_out[n16 + i] = 0;
+}
+
 // Pass 1 for blocks of class CLS. A bitmap byte holds 8 blocks. Up to B = 512
 // a chunk fills whole bytes; above, 2, 4 or 8 chunks share one, so the
 // workgroup's waves put their bits together in LDS: at B = 4096 that takes 8
@@ -688,7 +703,8 @@ __global__ __launch_bounds__(64 * enc_waves(CLS)) void encode_pass_kernel(
   constexpr bool OUT = DET != kDetHashOnly;
   constexpr int W = enc_waves(CLS);
   __shared__ uint32_t s_bits[W];
-  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // Workgroup L = 8k + x runs on XCD x as its k-th. With runs of
   // G = 2^a.xcd_run_log2 workgroups it takes the tiles of workgroup
   // (k / G) 8G + x G + k mod G, so each XCD streams G neighbouring
@@ -759,16 +775,8 @@ __global__ __launch_bounds__(64 * enc_waves(CLS)) void encode_pass_kernel(
   }
   if ((ELEMS || a.scan_prefix) && lane == 0) a.counts[tile] = count;
 
-  // the last tile zeroes the padding of the first two sections, before the
-  // exception pass reads the bitmap back
-  if (tile == a.num_tiles - 1) {
-    for (uint64_t i = S_sm + lane; i < n16; i += 64) sm_out[i] = 0;
-    uint64_t written = bm;
-    if (!ELEMS)
-      written = ((uint64_t(a.num_tiles) << (12 - log2B)) + 7) >> 3;
-    if (written > bm16) written = bm16;
-    for (uint64_t i = written + lane; i < bm16; i += 64) bmp_out[i] = 0;
-  }
+  // before the exception pass reads the bitmap back
+  if (tile == a.num_tiles - 1) pad_sections<ELEMS, F16>(a, lane);
 }
 
 // Exclusive scan of `count` 32-bit counts per segment, in place, one
@@ -921,12 +929,21 @@ struct ExcSrc {
   }
 };
 
+// Whether the shard's last block is flagged in its bitmap (B >= 16).
+__device__ __forceinline__ bool last_block_changed(const EncArgs &a,
+                                                   const uint8_t *bmp) {
+  const uint64_t nblk = blocks_of(a.n, a.log2B);
+  if (!nblk) return false;
+  return (bmp[(nblk - 1) >> 3] >> ((nblk - 1) & 7u)) & 1u;
+}
+
 // The totals, known to the wave that holds the last tile: the header, the
 // exception section's zero padding and the encoded size. total_changed
-// counts changed blocks (B >= 16) or changed values (B = 1).
+// counts changed blocks (B >= 16; last_changed: the last block is one of
+// them) or changed values (B = 1).
 template <bool ELEMS, bool F16>
 __device__ void exc_finish(const EncArgs &a, uint64_t total_changed,
-                           uint32_t lane) {
+                           uint32_t lane, bool last_changed) {
   const uint64_t n = a.n;
   const uint32_t log2B = a.log2B;
   const uint32_t B = 1u << log2B;
@@ -934,18 +951,12 @@ __device__ void exc_finish(const EncArgs &a, uint64_t total_changed,
   const uint64_t n16 = pad16(S_sm);
   const uint64_t bm = bitmap_bytes(n, log2B);
   const uint64_t bm16 = pad16(bm);
-  const uint8_t *const bmp = a.out + kHeaderBytes + n16;
   uint8_t *const exc_out = a.out + kHeaderBytes + n16 + bm16;
   uint64_t E = total_changed;
   if (!ELEMS) {
     E = total_changed << log2B;
-    const uint64_t nblk = blocks_of(n, log2B);
-    if (nblk) {
-      const uint64_t lb = nblk - 1;
-      const bool last_changed = (bmp[lb >> 3] >> (lb & 7u)) & 1u;
-      const uint64_t len_last = n - (lb << log2B);
-      if (last_changed) E -= (uint64_t(B) - len_last);
-    }
+    // the last block may be short
+    if (last_changed) E -= (blocks_of(n, log2B) << log2B) - n;
   }
   if (E > n) {  // only with a count array that was written by someone else
     if (lane == 0) set_error(a.ctl, CIERA_DEVERR_BOUNDS);
@@ -1052,7 +1063,7 @@ __global__ __launch_bounds__(kThreads) void encode_exc_elems_kernel(
   if (tile == nt - 1)
     exc_finish<true, false>(
         a, a.scan_prefix ? uint64_t(a.counts[nt]) : uint64_t(prefix) + run,
-        lane);
+        lane, false);
 }
 
 // Pass 2 for B >= 512. A row of 512 values lies inside one block, so it is
@@ -1178,7 +1189,8 @@ __global__ __launch_bounds__(kThreads) void encode_exc_rows_kernel(EncArgs a) {
       const uint32_t skip = i == (b0 >> 3) ? uint32_t(b0 & 7u) : 0u;
       own += __popc(uint32_t(bmp[i]) >> skip);
     }
-    exc_finish<false, F16>(a, uint64_t(prefix) + wave_sum(own), lane);
+    exc_finish<false, F16>(a, uint64_t(prefix) + wave_sum(own), lane,
+                           last_block_changed(a, bmp));
   }
 }
 
@@ -1304,8 +1316,152 @@ __global__ __launch_bounds__(kThreads) void encode_exc_blocks_kernel(
     uint32_t own = 0;
     for (uint64_t i = t0 * bpt + lane; i < min(t1 * bpt, bm); i += 64)
       own += __popc(uint32_t(bmp[i]));
-    exc_finish<false, F16>(a, uint64_t(prefix) + wave_sum(own), lane);
+    exc_finish<false, F16>(a, uint64_t(prefix) + wave_sum(own), lane,
+                           last_block_changed(a, bmp));
   }
+}
+
+// The whole encode of a small shard (up to kEncSmall values) in one launch of
+// one workgroup: 16 waves take a chunk each, put their counts together in LDS
+// and write their changed exponents from registers (more chunks than waves:
+// round after round with the running count). A second kernel, and the re-read of what it copies,
+// would cost more than the other CUs could save. Bound by latency: load,
+// compare, count across the waves, store (4.2 us at 128 values against 5.4 for
+// the two kernels, and one launch of 2.5 us less on the host).
+constexpr int kSmallThreads = 1024;
+template <bool ELEMS, int DET, bool F16, bool BIG>
+__global__ __launch_bounds__(kSmallThreads) void encode_small_kernel(
+    EncArgs a) {
+  constexpr uint32_t W = kSmallThreads / 64;
+  __shared__ uint32_t s_cnt[W];
+  __shared__ uint32_t s_bits[W];
+  __shared__ uint32_t s_last;
+  uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t n = a.n;
+  const uint32_t log2B = a.log2B;
+  const uint64_t n16 = pad16(sm_bytes(n, F16));
+  const uint64_t bm16 = pad16(bitmap_bytes(n, log2B));
+  uint8_t *const sm_out = a.out + kHeaderBytes;
+  uint8_t *const bmp_out = sm_out + n16;
+  uint8_t *const exc_out = bmp_out + bm16;
+  uint32_t carry = 0;  // changed blocks (B = 1: values) of the rounds before
+  if (threadIdx.x == 0) s_last = 0;
+  for (uint32_t t0 = 0; t0 < a.num_tiles; t0 += W) {
+    // opaque to the compiler in every round: it would otherwise keep what it
+    // derives from the lane in registers across rounds (128 VGPRs and scratch)
+    asm volatile("" : "+v"(lane));
+    const uint32_t tile = t0 + wave;
+    const bool live = tile < a.num_tiles;
+    const uint64_t cbase = uint64_t(tile) * kEncChunk;
+    uint32_t mask[8], excl[8], count = 0;
+    uint2 e[8];
+    uint64_t fw[4];
+    if (live) {
+      encode_chunk<ELEMS, DET, F16, true, BIG>(a, cbase, lane, sm_out, e, mask,
+                                               fw);
+      if (ELEMS) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
+          if (elem < n) bmp_out[elem >> 3] = uint8_t(mask[u]);
+          const uint32_t c = __popc(mask[u]);
+          const uint32_t incl = wave_incl_scan(c);
+          excl[u] = count + incl - c;
+          count += __builtin_amdgcn_readlane(incl, 63);
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) count += uint32_t(__popcll(fw[k]));
+        const uint32_t nb = kEncChunk >> log2B;  // blocks in a chunk
+        if (!BIG) {
+          const uint64_t byte0 = uint64_t(tile) * (nb >> 3);
+          for (uint32_t i = lane; i < (nb >> 3); i += 64)
+            if (byte0 + i < bm16)
+              bmp_out[byte0 + i] =
+                  uint8_t(pick<4>(fw, i >> 3) >> ((i & 7u) * 8u));
+        } else if (lane == 0) {
+          s_bits[wave] = uint32_t(fw[0]);
+        }
+        // the last block's flag decides the list's length
+        const uint64_t lb = blocks_of(n, log2B) - 1;
+        if (n && tile == a.num_tiles - 1 && lane == 0) {
+          const uint32_t k = uint32_t(lb - (cbase >> log2B));
+          s_last = uint32_t(pick<4>(fw, k >> 6) >> (k & 63u)) & 1u;
+        }
+      }
+    } else if (BIG && lane == 0) {
+      s_bits[wave] = 0;
+    }
+    if (lane == 0) s_cnt[wave] = count;
+    __syncthreads();
+    uint32_t before = carry, total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < W; ++w) {
+      const uint32_t c = s_cnt[w];
+      before += w < wave ? c : 0u;
+      total += c;
+    }
+    carry += total;
+    if (BIG) {
+      // byte i of the round: the bits of 8 / nb chunks
+      const uint32_t nb_log2 = 12 - log2B, cpb_log2 = log2B - 9;
+      const uint64_t pos = (uint64_t(t0) >> cpb_log2) + threadIdx.x;
+      if (threadIdx.x < (W >> cpb_log2) && pos < bm16) {
+        uint32_t b = 0;
+        for (uint32_t i = 0; i < (1u << cpb_log2); ++i)
+          b |= s_bits[(threadIdx.x << cpb_log2) + i] << (i << nb_log2);
+        bmp_out[pos] = uint8_t(b);
+      }
+    }
+    if (live && ELEMS) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        uint32_t mm = mask[u], pos = before + excl[u];
+        while (mm) {
+          exc_out[pos++] = uint8_t(octet_byte(e[u], __builtin_ctz(mm)));
+          mm &= mm - 1u;
+        }
+      }
+    } else if (live) {
+      const uint32_t left =
+          uint32_t(min(n - cbase, uint64_t(kEncChunk)));  // values from cbase
+      uint32_t in_front[4];  // flags in the words in front of each
+      uint32_t run = before;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        in_front[k] = run;
+        run += uint32_t(__popcll(fw[k]));
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t rel = uint32_t(u) * 512u + lane * 8u;
+        const uint32_t b = rel >> log2B;
+        // a unit's blocks share one word of the flags
+        const uint32_t q = (uint32_t(u) * 512u >> log2B) >> 6;
+        const uint64_t word =
+            q == 0 ? fw[0] : q == 1 ? fw[1] : q == 2 ? fw[2] : fw[3];
+        const uint32_t front = q == 0   ? in_front[0]
+                               : q == 1 ? in_front[1]
+                               : q == 2 ? in_front[2]
+                                        : in_front[3];
+        // (no flag past n; the exponents past n in the last octet are 0, as
+        // the padding that they fall into)
+        if (rel < left && ((word >> (b & 63u)) & 1u)) {
+          const uint32_t rank =
+              front +
+              uint32_t(__popcll(word & ((1ull << (b & 63u)) - 1ull)));
+          put_exc_exps<F16>(exc_out,
+                            (rank << log2B) | (rel & ((1u << log2B) - 1u)),
+                            e[u], 8);
+        }
+      }
+    }
+    if (tile == a.num_tiles - 1) pad_sections<ELEMS, F16>(a, lane);
+    __syncthreads();  // s_cnt and s_bits are read, s_last is written
+  }
+  if (wave == 0)
+    exc_finish<ELEMS, F16>(a, carry, lane, s_last != 0);
 }
 
 // Raw form: header + the values unchanged. One octet per lane.
@@ -1978,7 +2134,35 @@ void launch_exc(dim3 grid, const EncArgs &a, bool f16, bool fromc,
 }
 }  // namespace
 
+namespace {
+hipError_t launch_encode_small(const EncArgs &a, hipStream_t s) {
+  auto go = [&](auto e, auto det, auto f, auto big) {
+    hipLaunchKernelGGL((encode_small_kernel<decltype(e)::value,
+                                            decltype(det)::value,
+                                            decltype(f)::value,
+                                            decltype(big)::value>),
+                       dim3(1), dim3(kSmallThreads), 0, s, a);
+  };
+  auto blocks = [&](auto det, auto f) {
+    if (enc_class(a.log2B) == kInUnit)
+      go(bool_c<false>{}, det, f, bool_c<false>{});
+    else
+      go(bool_c<false>{}, det, f, bool_c<true>{});
+  };
+  if (a.log2B == 0)
+    go(bool_c<true>{}, int_c<kDetExact>{}, bool_c<false>{}, bool_c<false>{});
+  else if (a.f16)
+    blocks(int_c<kDetExact>{}, bool_c<true>{});
+  else if (a.hashed)
+    blocks(int_c<kDetHash>{}, bool_c<false>{});
+  else
+    blocks(int_c<kDetExact>{}, bool_c<false>{});
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_encode(const EncArgs &a, hipStream_t s) {
+  if (a.n <= kEncSmall) return launch_encode_small(a, s);
   const dim3 grid((a.num_tiles + 3) / 4);
   const bool elems = a.log2B == 0;
   // with the fused cache update the exception pass reads the cache, not W'
