@@ -203,7 +203,10 @@ def ciera_select(gains, mems, budget_bytes, flags=0):
 # ---- tensor-level marshalling ----
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream's handle. Asked for directly: the Stream object that
+    torch.cuda.current_stream() builds around it costs 2.8 us a call, as much
+    as a kernel launch; this takes 0.3."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
