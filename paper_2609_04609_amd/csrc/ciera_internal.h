@@ -170,6 +170,22 @@ struct DecArgs {
 __host__ __device__ inline uint64_t dec_tiles(uint64_t n) {
   return (n + kDecTile - 1) / kDecTile;
 }
+// Small layers: few tiles of 16384 values would leave CUs idle, so the decode
+// takes tiles of kDecOctSmall octets a lane. Every tile then counts the bitmap
+// in front of it, at B = 1 too (no count kernel), so that re-reading must stay
+// small as well. Two decodes from a HIP graph, 16384- against 4096-value
+// tiles: 16 shards of 8,192 values 14.4 / 6.8 us, of 131,072 (128 large tiles)
+// 11.1 / 10.8 us, in fp16 19.8 / 13.0, at B = 1 18.9 / 10.4; of 262,144 (256
+// large tiles) 13.4 / 14.2 us, where the line lies; 8192-value tiles come out
+// between the two on either side (7.0, 10.6, 15.2, 11.0 and 12.8 us).
+constexpr uint32_t kDecOctSmall = 2;
+inline bool dec_small(uint64_t n, uint32_t nshards, uint32_t log2B) {
+  constexpr uint64_t kMaxReread = uint64_t(16) << 20;
+  const uint64_t groups = dec_tiles(n) * nshards;
+  return groups < 256 &&
+         groups * (kDecOct / kDecOctSmall) * bitmap_bytes(n, log2B) / 2 <=
+             kMaxReread;
+}
 // decode: per-shard count segments (tiles + total), 16-byte aligned
 __host__ __device__ inline uint64_t dec_count_stride(uint64_t tiles) {
   return (tiles + 1 + 3) & ~uint64_t(3);

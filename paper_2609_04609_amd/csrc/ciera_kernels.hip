@@ -31,7 +31,8 @@
 //            so decode tiles never wait on each other. At B = 1 a count
 //            kernel takes every tile's bitmap bits first, and each tile adds
 //            up the counts in front of it (or, past 128 MB of such reads, a
-//            scan of the counts runs in between).
+//            scan of the counts runs in between). Small layers take smaller
+//            tiles and one kernel at every B (dec_small).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -2047,13 +2048,19 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
       }
     }
   }
-  // the changed values in front of the tile: scanned, or the counts in
-  // front of it added up here, its loads behind the tile's own
-  const uint32_t *const counts =
-      a.tile_excl + uint64_t(j) * dec_count_stride(tiles);
-  const uint32_t tile_first =
-      a.prefix_pass ? counts[t]
-                    : block_sum(sum_words_part<kGroupLoads>(counts, t), s_red);
+  // the changed values in front of the tile: counted from the bitmap (small
+  // layers, no count kernel), scanned, or the counts in front of it added up
+  // here, the loads of either sum behind the tile's own
+  uint32_t tile_first;
+  if constexpr (OCT != int(kDecOct)) {
+    tile_first = block_sum(popc_bytes_part<kGroupLoads>(bmp, base >> 3), s_red);
+  } else {
+    const uint32_t *const counts =
+        a.tile_excl + uint64_t(j) * dec_count_stride(tiles);
+    tile_first = a.prefix_pass
+                     ? counts[t]
+                     : block_sum(sum_words_part<kGroupLoads>(counts, t), s_red);
+  }
   uint32_t excl[OCT];
   rank_octets<OCT>(cnt, excl, s_seg);
 
@@ -2249,42 +2256,55 @@ hipError_t launch_encode_raw(const uint16_t *w, uint64_t n, uint32_t B,
   return hipGetLastError();
 }
 
+namespace {
+template <int OCT>
+void launch_decode_tiles(const DecArgs &a, hipStream_t s) {
+  constexpr uint64_t T = uint64_t(kThreads) * 8 * OCT;
+  const dim3 grid(uint32_t((a.n + T - 1) / T), a.nshards), block(kThreads);
+  const bool upd = a.out == nullptr;
+  if (a.log2B == 0) {
+    if (upd)
+      hipLaunchKernelGGL((decode_elems_kernel<OCT, true>), grid, block, 0, s,
+                         a);
+    else
+      hipLaunchKernelGGL((decode_elems_kernel<OCT, false>), grid, block, 0, s,
+                         a);
+  } else if (a.f16) {
+    if (upd)
+      hipLaunchKernelGGL((decode_kernel<OCT, true, true>), grid, block, 0, s,
+                         a);
+    else
+      hipLaunchKernelGGL((decode_kernel<OCT, false, true>), grid, block, 0, s,
+                         a);
+  } else {
+    if (upd)
+      hipLaunchKernelGGL((decode_kernel<OCT, true>), grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL((decode_kernel<OCT, false>), grid, block, 0, s, a);
+  }
+}
+}  // namespace
+
 hipError_t launch_decode(const DecArgs &a, hipStream_t s) {
   const uint64_t tiles = dec_tiles(a.n);
   if (tiles == 0 || a.nshards == 0) return hipSuccess;
-  const dim3 grid(uint32_t(tiles), a.nshards), block(kThreads);
-  const bool upd = a.out == nullptr;
-  constexpr int O = int(kDecOct);
+  if (dec_small(a.n, a.nshards, a.log2B)) {
+    launch_decode_tiles<int(kDecOctSmall)>(a, s);
+    return hipGetLastError();
+  }
   if (a.log2B == 0) {
-    const dim3 cgrid(uint32_t((tiles + 3) / 4), a.nshards);
-    hipLaunchKernelGGL(count_tile_bits_kernel, cgrid, block, 0, s, a,
-                       uint32_t(tiles));
+    hipLaunchKernelGGL(count_tile_bits_kernel,
+                       dim3(uint32_t((tiles + 3) / 4), a.nshards),
+                       dim3(kThreads), 0, s, a, uint32_t(tiles));
     if (a.prefix_pass)
       hipLaunchKernelGGL(scan_counts_kernel, dim3(a.nshards),
                          dim3(kScanThreads), 0, s, a.tile_excl,
                          uint32_t(tiles), dec_count_stride(tiles));
-    if (upd)
-      hipLaunchKernelGGL((decode_elems_kernel<O, true>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((decode_elems_kernel<O, false>), grid, block, 0, s,
-                         a);
-    return hipGetLastError();
-  }
-  if (a.prefix_pass)
+  } else if (a.prefix_pass) {
     hipLaunchKernelGGL(tile_prefix_kernel, dim3(a.nshards), dim3(kScanThreads),
                        0, s, a);
-  if (a.f16) {
-    if (upd)
-      hipLaunchKernelGGL((decode_kernel<O, true, true>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((decode_kernel<O, false, true>), grid, block, 0, s,
-                         a);
-  } else {
-    if (upd)
-      hipLaunchKernelGGL((decode_kernel<O, true>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((decode_kernel<O, false>), grid, block, 0, s, a);
   }
+  launch_decode_tiles<int(kDecOct)>(a, s);
   return hipGetLastError();
 }
 

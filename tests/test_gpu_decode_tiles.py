@@ -1,0 +1,86 @@
+"""The gathered decode and the cache update on both sides of the line between
+small layers (tiles of 4096 values, the bitmap counted in every tile) and the
+rest (16384), at the edges of tiles, against the oracle's splits and the
+weights themselves: whole, cut and single-octet last tiles, one shard of the
+gather raw, buffers at odd places."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_util
+    from paper_2609_04609_amd import ciera
+    ciera.lib()
+    return gpu_util
+
+
+# (shards, values per shard): 16384-value tiles times shards reaches 256 in
+# the last six
+SHAPES = [(1, 1), (5, 4095), (5, 4096), (4, 4097), (16, 16_385),
+          (3, 12 * 4096 + 9), (255, 16_384), (256, 16_384), (256, 16_381),
+          (4, 1_048_577), (4, 1_064_960), (1, 255 * 16_384 + 1),
+          (2, 3_000_001)]
+
+
+@pytest.mark.parametrize("fp16", [False, True])
+@pytest.mark.parametrize("B", [1, 16, 512, 4096])
+def test_decode_tile_edges(gu, orc, B, fp16):
+    from paper_2609_04609_amd import ciera, synth
+    if fp16 and B == 1:
+        pytest.skip("fp16 shards need B >= 16")
+    flags = ciera.FP16 if fp16 else 0
+    split = orc.split_f16 if fp16 else orc.split
+    for k, (R, n) in enumerate(SHAPES):
+        msg = f"R={R} n={n} B={B} fp16={fp16}"
+        if fp16:
+            w = synth.normal_f16_bits(R * n, 0.02, 50 + k)
+            w2 = synth.forced_bernoulli_f16_bits(w, 0.002, 51 + k)
+        else:
+            w, w2 = gu.pair(R * n, 50 + k, c=0.002)
+        e2 = split(gu.host_u16(w2))[0]
+        cache_h = split(gu.host_u16(w))[0]
+        old = gu.dev_u8(cache_h)
+        bound = int(ciera.ciera_encoded_bound(n, B, flags))
+        g = torch.empty(R * bound, dtype=torch.uint8, device="cuda")
+        offs = torch.arange(R, dtype=torch.int64, device="cuda") * bound
+        ws = ciera.Workspace(n, R, B)
+        raw = R // 2 if R > 1 else -1
+        for j in range(R):
+            own = slice(j * n, (j + 1) * n)
+            ciera.encode_t(w2[own], None if j == raw else old[own], B, ws,
+                           g[j * bound:(j + 1) * bound], raw=j == raw,
+                           fp16=fp16)
+        if k < 6:  # the shards themselves are the oracle's
+            for j in range(R):
+                own = slice(j * n, (j + 1) * n)
+                enc = (orc.encode_f16 if fp16 else orc.encode)(
+                    gu.host_u16(w2[own]), None if j == raw else cache_h[own],
+                    B, raw=j == raw)
+                np.testing.assert_array_equal(
+                    gu.host_u8(g[j * bound:j * bound + enc.size]), enc,
+                    err_msg=msg)
+        for shift in (0, 3):
+            cbuf = torch.full((R * n + 16,), 0x5A, dtype=torch.uint8,
+                              device="cuda")
+            cache = cbuf[shift:shift + R * n]
+            cache.copy_(old)
+            obuf = torch.zeros(R * n + 16, dtype=torch.int16, device="cuda")
+            out = obuf[shift:shift + R * n]
+            ciera.decode_gathered_t(g, offs, n, B, out, cache, ws, fp16=fp16)
+            assert torch.equal(out, w2), msg
+            np.testing.assert_array_equal(gu.host_u8(cache), e2, err_msg=msg)
+            assert (cbuf[shift + R * n:] == 0x5A).all(), msg
+            assert (obuf[shift + R * n:] == 0).all(), msg
+        for j in {0, R - 1}:
+            own = slice(j * n, (j + 1) * n)
+            c = old[own].clone()
+            ciera.update_cache_t(c, g[j * bound:(j + 1) * bound], n, B, ws,
+                                 fp16=fp16)
+            np.testing.assert_array_equal(gu.host_u8(c), e2[own], err_msg=msg)
+        assert ws.error() == 0, msg
