@@ -6,13 +6,20 @@
 // format is given in include/ciera.h.
 //
 // Coding (ciera_ans_code), in place on an encoded shard:
-//   ans_hist_kernel      byte histogram of the exception list
-//   ans_table_kernel     quantised frequencies (sum 4096) and cumulatives
-//   ans_encode_kernel    every chunk backwards; words go to the end of the
-//                        chunk's workspace slot, lane order within a step
-//   ans_finalize_kernel  stream offsets, the size decision, section tables
-//                        and header (only when the coded section is smaller)
-//   ans_copy_kernel      the chunk streams into the section
+//   ans_hist_kernel    byte histogram of the exception list, a row of counts
+//                      per workgroup
+//   ans_encode_kernel  every workgroup adds up the rows and quantises the
+//                      frequencies (sum 4096) for itself, then every wave codes
+//                      chunks backwards; words go to the end of the chunk's
+//                      workspace slot, lane order within a step
+//   ans_copy_kernel    every workgroup adds up the stream sizes: the size
+//                      decision and its chunks' offsets; then section tables,
+//                      header and the chunk streams (only when the coded
+//                      section is smaller)
+// or, for shards of up to kAnsSmallChunks chunks, all of it in one workgroup
+// (ans_code_small_kernel). What the kernels compute again in every workgroup
+// is less than a launch of one workgroup that computes it once: 4.5 to 5 us
+// each for zeroing the counters, the table and the offsets.
 // Decoding (inside ciera_decode_gathered / ciera_update_cache):
 //   ans_decode_kernel    every chunk of every rANS-coded shard into the
 //                        shard's exception list in the workspace; the decode
@@ -20,6 +27,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "ciera.h"
@@ -29,7 +37,6 @@ namespace ciera {
 
 namespace {
 
-constexpr int kWaves = kThreads / 64;
 #ifndef CIERA_ANS_DEC_THREADS
 #define CIERA_ANS_DEC_THREADS 1024
 #endif
@@ -57,7 +64,8 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
                                    __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
 }
 
-// Block-wide sum and exclusive scan of one value per thread.
+// Workgroup-wide sum and exclusive scan of one value per thread, NW waves.
+template <int NW>
 __device__ uint32_t block_sum32(uint32_t v, uint32_t *s_red) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -67,10 +75,11 @@ __device__ uint32_t block_sum32(uint32_t v, uint32_t *s_red) {
   __syncthreads();
   uint32_t t = 0;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) t += s_red[w];
+  for (int w = 0; w < NW; ++w) t += s_red[w];
   return t;
 }
 
+template <int NW>
 __device__ uint32_t block_excl_scan32(uint32_t v, uint32_t *s_red,
                                       uint32_t *total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -85,7 +94,7 @@ __device__ uint32_t block_excl_scan32(uint32_t v, uint32_t *s_red,
   __syncthreads();
   uint32_t before = 0, all = 0;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
+  for (int w = 0; w < NW; ++w) {
     if (w < wave) before += s_red[w];
     all += s_red[w];
   }
@@ -93,10 +102,12 @@ __device__ uint32_t block_excl_scan32(uint32_t v, uint32_t *s_red,
   return before + inc - v;
 }
 
-// The thread holding the largest v (lowest index on ties) among the block.
+// The symbol (thread idx < 256) holding the largest v, the lowest on ties.
+// Some v is above 0; threads past 255 pass 0.
+template <int NW>
 __device__ uint32_t block_argmax(uint64_t v, uint32_t idx, uint64_t *s_key) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint64_t key = (v << 8) | uint64_t(255u - idx);
+  uint64_t key = idx < 256 ? (v << 8) | uint64_t(255u - idx) : 0ull;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     const uint64_t o = __shfl_xor(key, off, 64);
@@ -107,35 +118,43 @@ __device__ uint32_t block_argmax(uint64_t v, uint32_t idx, uint64_t *s_key) {
   __syncthreads();
   uint64_t best = s_key[0];
 #pragma unroll
-  for (int w = 1; w < kWaves; ++w) best = s_key[w] > best ? s_key[w] : best;
+  for (int w = 1; w < NW; ++w) best = s_key[w] > best ? s_key[w] : best;
   return 255u - uint32_t(best & 255u);
 }
 
 // ================================================================ coding ==
 
+// The number of exception bytes to code, 0 for a shard that stays as it is.
+__device__ __forceinline__ uint64_t ans_to_code(const AnsEncArgs &a) {
+  const uint64_t E = ld64(a.enc + 32);
+  if ((ld32(a.enc + 4) >> 16) != kModeCompressed ||
+      ld32(a.enc + 12) != kDtypeBf16 || E > a.n)
+    return 0;
+  return E;
+}
+
+// Row g of the histogram: 256 counts at the start of chunk g's slot of words.
+// A chunk's words end at most 64 * 49 words from the slot's end (each state
+// takes up 16 bits a word and 12 bits a symbol), so coding leaves it alone.
+__device__ __forceinline__ uint32_t *hist_row(const AnsEncArgs &a,
+                                              uint32_t g) {
+  return reinterpret_cast<uint32_t *>(a.words + uint64_t(g) * kAnsChunk);
+}
+static_assert((kAnsChunk - 64 * 49) * 2 >= 1024, "a row fits in front");
+
 // The exponents of the changed blocks crowd into a few values, so the lanes
 // of one instruction adding into a single LDS histogram would mostly hit the
 // same counters. The workgroup keeps kHistCopies copies, thread t adding into
 // copy t mod kHistCopies; a copy is 257 words long, so one symbol's counters
-// in different copies fall in different LDS banks.
+// in different copies fall in different LDS banks. Counts exception bytes
+// first, first + stride, ... (16 at a time); s_h is zero before.
 constexpr int kHistCopies = 16;
 constexpr int kHistStride = 257;
-__global__ __launch_bounds__(kThreads) void ans_hist_kernel(AnsEncArgs a) {
-  __shared__ uint32_t s_h[kHistCopies * kHistStride];
-  const uint8_t *enc = a.enc;
-  const uint32_t mode = ld32(enc + 4) >> 16;
-  const uint64_t E = ld64(enc + 32);
-  if (mode != kModeCompressed || ld32(enc + 12) != kDtypeBf16 || E == 0 ||
-      E > a.n)
-    return;
-  const int tid = threadIdx.x;
-  for (int i = tid; i < kHistCopies * kHistStride; i += kThreads) s_h[i] = 0u;
-  __syncthreads();
-  uint32_t *const h = s_h + (tid & (kHistCopies - 1)) * kHistStride;
-  const uint8_t *exc = enc + exc_offset(a.n, a.log2B);
-  const uint64_t stride = uint64_t(gridDim.x) * kThreads * 16;
-  for (uint64_t i = (uint64_t(blockIdx.x) * kThreads + tid) * 16; i < E;
-       i += stride) {
+__device__ __forceinline__ void hist_bytes(const uint8_t *exc, uint64_t E,
+                                           uint64_t first, uint64_t stride,
+                                           uint32_t *s_h) {
+  uint32_t *const h = s_h + (threadIdx.x & (kHistCopies - 1)) * kHistStride;
+  for (uint64_t i = first; i < E; i += stride) {
     if (i + 16 <= E) {
       const uint4 v = *reinterpret_cast<const uint4 *>(exc + i);
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -148,234 +167,402 @@ __global__ __launch_bounds__(kThreads) void ans_hist_kernel(AnsEncArgs a) {
       for (uint64_t k = i; k < E; ++k) atomicAdd(&h[exc[k]], 1u);
     }
   }
-  __syncthreads();
-  uint32_t t = 0;
-#pragma unroll
-  for (int c = 0; c < kHistCopies; ++c) t += s_h[c * kHistStride + tid];
-  if (t) atomicAdd(&a.ans->hist[tid], t);
 }
 
-// One workgroup; thread s owns symbol s. Quantisation: every present symbol
-// gets max(1, floor(h_s M / E)); a deficit goes to the most frequent symbol,
-// an excess comes off the largest frequency (lowest symbol on ties), never
-// below 1, until the total is M.
-__global__ __launch_bounds__(kThreads) void ans_table_kernel(AnsEncArgs a) {
-  __shared__ uint32_t s_red[kWaves];
-  __shared__ uint64_t s_key[kWaves];
-  __shared__ uint32_t s_fbest;
-  const uint32_t s = threadIdx.x;
-  const uint32_t mode = ld32(a.enc + 4) >> 16;
-  const uint64_t E = ld64(a.enc + 32);
-  if (mode != kModeCompressed || ld32(a.enc + 12) != kDtypeBf16 || E == 0 ||
-      E > a.n) {
-    if (s == 0) a.ans->K = 0;
-    return;
+// Bound by the latency of its loads until 4096 waves run: 128 workgroups of
+// 512 threads left the coding of the OLMoE shard 2 us and of a shard with
+// every exponent sent 8 us slower than 256 of 1024; more rows than that would
+// cost the coder as much to add up.
+constexpr int kHistThreads = 1024;
+constexpr uint32_t kHistRows = 256;  // workgroups of ans_hist_kernel at most
+__global__ __launch_bounds__(kHistThreads) void ans_hist_kernel(AnsEncArgs a) {
+  __shared__ uint32_t s_h[kHistCopies * kHistStride];
+  const uint64_t E = ans_to_code(a);
+  if (E == 0) return;
+  const int tid = threadIdx.x;
+  for (int i = tid; i < kHistCopies * kHistStride; i += kHistThreads)
+    s_h[i] = 0u;
+  __syncthreads();
+  hist_bytes(a.enc + exc_offset(a.n, a.log2B), E,
+             (uint64_t(blockIdx.x) * kHistThreads + tid) * 16,
+             uint64_t(gridDim.x) * kHistThreads * 16, s_h);
+  __syncthreads();
+  if (tid < 256) {
+    uint32_t t = 0;
+#pragma unroll
+    for (int c = 0; c < kHistCopies; ++c) t += s_h[c * kHistStride + tid];
+    hist_row(a, blockIdx.x)[tid] = t;
   }
-  const uint32_t h = a.ans->hist[s];
+}
+
+// Thread s < 256 owns symbol s with count h (the others: h = 0). Quantisation:
+// every present symbol gets max(1, floor(h_s M / E)); a deficit goes to the
+// most frequent symbol, an excess comes off the largest frequency (lowest
+// symbol on ties), never below 1, until the total is M. Returns the frequency;
+// *cum its exclusive prefix sum.
+struct TableScratch {
+  uint32_t red[16];
+  uint64_t key[16];
+  uint32_t fbest;
+};
+template <int NW>
+__device__ __forceinline__ uint32_t quantise(uint32_t h, uint64_t E,
+                                             uint32_t *cum, TableScratch &t) {
+  const uint32_t s = threadIdx.x;
   uint32_t f = 0;
   if (h) {
     const uint64_t q = (uint64_t(h) << kAnsScale) / E;
     f = q ? uint32_t(q) : 1u;
   }
-  uint32_t sum = block_sum32(f, s_red);
+  uint32_t sum = block_sum32<NW>(f, t.red);
   if (sum < kAnsM) {
-    const uint32_t best = block_argmax(h, s, s_key);
+    const uint32_t best = block_argmax<NW>(h, s, t.key);
     if (s == best) f += kAnsM - sum;
     sum = kAnsM;
   }
   while (sum > kAnsM) {
-    const uint32_t best = block_argmax(f, s, s_key);
-    if (s == best) s_fbest = f;
+    const uint32_t best = block_argmax<NW>(f, s, t.key);
+    if (s == best) t.fbest = f;
     __syncthreads();
-    const uint32_t fbest = s_fbest;
+    const uint32_t fbest = t.fbest;
     uint32_t take = sum - kAnsM;
     if (take > fbest - 1u) take = fbest - 1u;
     if (s == best) f -= take;
     sum -= take;
   }
   uint32_t total = 0;
-  const uint32_t cum = block_excl_scan32(f, s_red, &total);
-  a.ans->freq[s] = f;
-  a.ans->cum[s] = cum;
-  if (s == 0) a.ans->K = uint32_t((E + kAnsChunk - 1) / kAnsChunk);
+  *cum = block_excl_scan32<NW>(f, t.red, &total);
+  return f;
 }
 
-// Persistent: a wave codes chunk c = (round * grid + workgroup) * 4 + wave;
-// every workgroup runs the same number of rounds so that its barriers match.
-__global__ __launch_bounds__(kThreads) void ans_encode_kernel(AnsEncArgs a) {
-  // per symbol: the reciprocal m of f, and f | cum << 13 | sh2 << 26 |
-  // sh1 << 30
-  __shared__ uint2 s_tab[256];
-  __shared__ __align__(16) uint8_t s_sym[kWaves][kAnsChunk];
-  const uint32_t K = a.ans->K;
-  if (K == 0) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  {
-    // x / f without a divide (Granlund and Montgomery 1994, division by
-    // invariant integers, Fig. 4.1): with l = ceil(log2 f) and
-    // m = floor(2^32 (2^l - f) / f) + 1 < 2^32, t = mulhi(x, m) gives
-    // x / f = (t + ((x - t) >> min(l, 1))) >> max(l - 1, 0) for every
-    // 32-bit x. Absent symbols (f = 0) are never coded.
-    const uint32_t f = a.ans->freq[tid], cm = a.ans->cum[tid];
-    const uint32_t l = f > 1u ? 32u - uint32_t(__clz(f - 1u)) : 0u;
-    const uint32_t m =
-        f ? uint32_t(((((uint64_t(1) << l) - f) << 32) / f) + 1u) : 0u;
-    const uint32_t sh1 = l < 1u ? l : 1u, sh2 = l > 1u ? l - 1u : 0u;
-    s_tab[tid] = make_uint2(m, f | (cm << 13) | (sh2 << 26) | (sh1 << 30));
-  }
-  const uint64_t E = ld64(a.enc + 32);
-  const uint8_t *exc = a.enc + exc_offset(a.n, a.log2B);
-  const uint32_t per_round = gridDim.x * kWaves;
-  const uint32_t rounds = (K + per_round - 1) / per_round;
-  for (uint32_t r = 0; r < rounds; ++r) {
-    const uint32_t c = (r * gridDim.x + blockIdx.x) * kWaves + wave;
-    const bool act = c < K;
-    const uint64_t lo = uint64_t(c) * kAnsChunk;
-    const uint32_t len =
-        act ? uint32_t(E - lo < kAnsChunk ? E - lo : kAnsChunk) : 0u;
-    __syncthreads();
-    for (uint32_t k = uint32_t(lane) * 16; k < len; k += 64 * 16) {
-      if (k + 16 <= len) {
-        *reinterpret_cast<uint4 *>(&s_sym[wave][k]) =
-            *reinterpret_cast<const uint4 *>(exc + lo + k);
-      } else {
-        for (uint32_t q = k; q < len; ++q) s_sym[wave][q] = exc[lo + q];
-      }
-    }
-    __syncthreads();
-    if (!act) continue;
-    uint32_t x = kAnsL;
-    uint32_t p = kAnsChunk;  // the words of this chunk fill [p, kAnsChunk)
-    uint16_t *slot = a.words + lo;
-    for (int t = int((len + 63) / 64) - 1; t >= 0; --t) {
-      const uint32_t i = uint32_t(t) * 64 + uint32_t(lane);
-      const bool live = i < len;
-      const uint2 e = s_tab[live ? s_sym[wave][i] : 0u];
-      const uint32_t f = e.y & 0x1FFFu, cm = (e.y >> 13) & 0xFFFu;
-      const bool emit = live && uint64_t(x) >= (uint64_t(f) << 20);
-      const uint64_t m = __ballot(emit);
-      const uint32_t cnt = uint32_t(__popcll(m));
-      if (emit) {
-        slot[p - cnt + lanes_below(m)] = uint16_t(x & 0xFFFFu);
-        x >>= 16;
-      }
-      p -= cnt;
-      if (live) {
-        const uint32_t t = __umulhi(x, e.x);
-        const uint32_t q =
-            (t + ((x - t) >> (e.y >> 30))) >> ((e.y >> 26) & 15u);
-        x = (q << kAnsScale) + (x - q * f) + cm;
-      }
-    }
-    a.states[uint64_t(c) * 64 + uint32_t(lane)] = x;
-    if (lane == 0) a.counts[c] = kAnsChunk - p;
-  }
+// A symbol's coding entry. x / f without a divide (Granlund and Montgomery
+// 1994, division by invariant integers, Fig. 4.1): with l = ceil(log2 f) and
+// m = floor(2^32 (2^l - f) / f) + 1 < 2^32, t = mulhi(x, m) gives
+// x / f = (t + ((x - t) >> min(l, 1))) >> max(l - 1, 0) for every 32-bit x.
+// y: the largest state that takes the symbol without a word, 2^20 f - 1;
+// z: M - f; w: cum, the shifts at bits 16 and 20. Absent symbols (f = 0) are
+// never coded.
+__device__ __forceinline__ uint4 coding_entry(uint32_t f, uint32_t cum) {
+  const uint32_t l = f > 1u ? 32u - uint32_t(__clz(f - 1u)) : 0u;
+  const uint32_t m =
+      f ? uint32_t(((((uint64_t(1) << l) - f) << 32) / f) + 1u) : 0u;
+  const uint32_t sh1 = l < 1u ? l : 1u, sh2 = l > 1u ? l - 1u : 0u;
+  return make_uint4(m, (f << 20) - 1u, kAnsM - f,
+                    cum | (sh1 << 16) | (sh2 << 20));
 }
 
-// One workgroup: chunk stream offsets (states + words, padded to 4 bytes),
-// the size decision, and when the coded section is smaller than E the
-// section's tables and the new header fields.
-__global__ __launch_bounds__(kThreads) void ans_finalize_kernel(AnsEncArgs a) {
-  __shared__ uint32_t s_red[kWaves];
+// One wave codes chunk c backwards: its final states and its words (at the end
+// of its slot) go to the workspace. Returns the words. A step's table entries
+// do not depend on the states, so those of kAhead steps are read before the
+// first of them is coded.
+__device__ __forceinline__ uint32_t code_chunk(const AnsEncArgs &a, uint32_t c,
+                                               const uint8_t *exc, uint64_t E,
+                                               const uint4 *s_tab,
+                                               uint8_t *s_sym) {
+  constexpr int kAhead = 4;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t lo = uint64_t(c) * kAnsChunk;
+  const uint32_t len = uint32_t(E - lo < kAnsChunk ? E - lo : kAnsChunk);
+  __builtin_amdgcn_wave_barrier();  // the previous chunk's symbols are read
+  if (len == kAnsChunk) {
+    const uint4 *src = reinterpret_cast<const uint4 *>(exc + lo) + lane;
+    uint4 *const dst = reinterpret_cast<uint4 *>(s_sym) + lane;
+    const uint4 v0 = src[0], v1 = src[64], v2 = src[128], v3 = src[192];
+    dst[0] = v0;
+    dst[64] = v1;
+    dst[128] = v2;
+    dst[192] = v3;
+  } else {
+    for (uint32_t b = lane; b < len; b += 64) s_sym[b] = exc[lo + b];
+  }
+  __builtin_amdgcn_wave_barrier();
+  uint32_t x = kAnsL;
+  uint32_t p = kAnsChunk;  // the words of this chunk fill [p, kAnsChunk)
+  uint16_t *const slot = a.words + lo;
+  auto step = [&](uint4 e, bool live) {
+    const bool emit = live && x > e.y;
+    const uint64_t m = __ballot(emit);
+    p -= uint32_t(__popcll(m));
+    if (emit) {
+      slot[p + lanes_below(m)] = uint16_t(x & 0xFFFFu);
+      x >>= 16;
+    }
+    const uint32_t t = __umulhi(x, e.x);
+    const uint32_t q = (t + ((x - t) >> ((e.w >> 16) & 1u))) >> (e.w >> 20);
+    // q M + (x - q f) + cum (q < 2^20)
+    const uint32_t xn = __umul24(q, e.z) + x + (e.w & 0xFFFFu);
+    x = live ? xn : x;
+  };
+  int t = int(len / 64) - 1;
+  if (len % 64) {  // only the last chunk's first step
+    const uint32_t i = uint32_t(t + 1) * 64 + lane;
+    step(s_tab[i < len ? s_sym[i] : 0u], i < len);
+  }
+  for (; t >= kAhead - 1; t -= kAhead) {
+    uint4 e[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+      e[k] = s_tab[s_sym[uint32_t(t - k) * 64 + lane]];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) step(e[k], true);
+  }
+  for (; t >= 0; --t) step(s_tab[s_sym[uint32_t(t) * 64 + lane]], true);
+  a.states[uint64_t(c) * 64 + lane] = x;
+  const uint32_t words = kAnsChunk - p;
+  if (lane == 0) a.counts[c] = words;
+  return words;
+}
+
+// A wave codes chunk (round * grid + workgroup) * waves + wave. Bound by
+// latency: the chain of 64 state updates, after the histogram rows.
+// OLMoE shard (10.1 MB of exceptions): the three kernels take 35 us, against 52
+// for a counter fill, histogram with global atomics, table, coder, offsets and
+// copy in six launches; 16 x 131,072 values with every block sent, coded and
+// decoded with the rest of the step, 47 against 62 us.
+constexpr int kCodeThreads = 512;
+constexpr uint32_t kCodeWaves = kCodeThreads / 64;
+__global__ __launch_bounds__(kCodeThreads) void ans_encode_kernel(
+    AnsEncArgs a, uint32_t rows) {
+  __shared__ uint4 s_tab[256];
+  __shared__ __align__(16) uint8_t s_sym[kCodeWaves][kAnsChunk];
+  __shared__ TableScratch s_t;
   const uint32_t tid = threadIdx.x;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t E = ans_to_code(a);
+  const uint32_t K = uint32_t((E + kAnsChunk - 1) / kAnsChunk);
+  if (blockIdx.x == 0 && tid == 0) a.ans->K = K;
+  if (blockIdx.x * kCodeWaves >= K) return;
+  // the rows, two threads a symbol, through the LDS the symbols take later
+  uint32_t h = 0;
+  {
+    constexpr uint32_t kParts = kCodeThreads / 256;
+    const uint32_t s = tid & 255u;
+#pragma unroll 32
+    for (uint32_t g = tid >> 8; g < rows; g += kParts) h += hist_row(a, g)[s];
+    uint32_t *const part = reinterpret_cast<uint32_t *>(&s_sym[0][0]);
+    part[tid] = h;
+    __syncthreads();
+    h = 0;
+    if (tid < 256)
+#pragma unroll
+      for (uint32_t q = 0; q < kParts; ++q) h += part[q * 256 + tid];
+  }
+  uint32_t cum;
+  const uint32_t f = quantise<kCodeWaves>(h, E, &cum, s_t);
+  if (tid < 256) {
+    s_tab[tid] = coding_entry(f, cum);
+    if (blockIdx.x == 0) a.ans->freq[tid] = f;
+  }
+  __syncthreads();
+  const uint8_t *exc = a.enc + exc_offset(a.n, a.log2B);
+  for (uint32_t c = blockIdx.x * kCodeWaves + wave; c < K;
+       c += gridDim.x * kCodeWaves)
+    code_chunk(a, c, exc, E, s_tab, s_sym[wave]);
+}
+
+// Bytes of chunk c's stream: the states and its words, padded to 4 bytes.
+__device__ __forceinline__ uint32_t stream_bytes(uint32_t words) {
+  return (256u + 2u * words + 3u) & ~3u;
+}
+
+// One wave copies chunk c's stream to the section, start bytes into the
+// streams; the last chunk (end bytes in) also zeroes the section's padding.
+__device__ __forceinline__ void copy_chunk(const AnsEncArgs &a, uint32_t c,
+                                           uint32_t K, uint8_t *sec,
+                                           uint32_t start, uint32_t end,
+                                           uint32_t words) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint8_t *const dst = sec + kAnsFixed + 4ull * K + start;
+  reinterpret_cast<uint32_t *>(dst)[lane] = a.states[uint64_t(c) * 64 + lane];
+  const uint16_t *src = a.words + uint64_t(c) * kAnsChunk + (kAnsChunk - words);
+  uint16_t *d16 = reinterpret_cast<uint16_t *>(dst + 256);
+  // 8 words a lane (16-byte accesses at the 2- and 4-byte aligned places that
+  // they start at), then the last few
+  typedef uint32_t words8_t __attribute__((ext_vector_type(4), aligned(2)));
+  const uint32_t whole = words & ~7u;
+#pragma unroll 2
+  for (uint32_t k = lane * 8; k < whole; k += 512)
+    *reinterpret_cast<words8_t *>(d16 + k) =
+        *reinterpret_cast<const words8_t *>(src + k);
+  if (whole + lane < words) d16[whole + lane] = src[whole + lane];
+  if ((words & 1u) && lane == 0) d16[words] = 0;
+  if (c == K - 1) {
+    const uint64_t C = kAnsFixed + 4ull * K + end;
+    for (uint64_t b = C + lane; b < pad16(C); b += 64) sec[b] = 0;
+  }
+}
+
+// The coded section's fixed part and the shard's new header fields, by the
+// first 256 threads (freq: symbol tid's frequency).
+__device__ __forceinline__ void put_section(const AnsEncArgs &a, uint32_t K,
+                                            uint8_t *sec, uint64_t C,
+                                            uint32_t freq) {
+  const uint32_t tid = threadIdx.x;
+  const uint64_t bm = bitmap_bytes(a.n, a.log2B);
+  if (tid < 256) reinterpret_cast<uint16_t *>(sec + 8)[tid] = uint16_t(freq);
+  if (tid == 0) {
+    reinterpret_cast<uint32_t *>(sec)[0] = K;
+    reinterpret_cast<uint32_t *>(sec)[1] = kAnsChunk;
+    const uint64_t total = kHeaderBytes + pad16(a.n) + pad16(bm) + pad16(C);
+    reinterpret_cast<uint32_t *>(a.enc)[1] = kVersion | (kModeAns << 16);
+    reinterpret_cast<uint64_t *>(a.enc)[5] = a.n + bm + C;
+    reinterpret_cast<uint64_t *>(a.enc)[6] = total;
+    if (a.out_bytes) *a.out_bytes = total;
+  }
+}
+
+// Workgroup b copies chunks [b per, (b + 1) per). The header's mode, P and
+// total change under the other workgroups, which read none of them.
+__global__ __launch_bounds__(kThreads) void ans_copy_kernel(AnsEncArgs a) {
+  constexpr int NW = kThreads / 64;
+  __shared__ uint32_t s_red[NW];
+  __shared__ uint32_t s_start[kThreads + 1];
+  const uint32_t tid = threadIdx.x;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t K = a.ans->K;
-  uint8_t *enc = a.enc;
-  const uint64_t old_total = ld64(enc + 48);
   if (K == 0) {
-    if (tid == 0) {
-      a.ans->coded = 0;
-      if (a.out_bytes) *a.out_bytes = old_total;
-    }
+    if (blockIdx.x == 0 && tid == 0 && a.out_bytes)
+      *a.out_bytes = ld64(a.enc + 48);
     return;
   }
-  const uint64_t n = a.n, E = ld64(enc + 32);
-  const uint64_t bm = bitmap_bytes(n, a.log2B);
-  const uint32_t per = (K + kThreads - 1) / kThreads;
-  const uint32_t k0 = tid * per < K ? tid * per : K;
-  const uint32_t k1 = k0 + per < K ? k0 + per : K;
-  uint32_t mine = 0;
-  for (uint32_t c = k0; c < k1; ++c)
-    mine += (256u + 2u * a.counts[c] + 3u) & ~3u;
-  uint32_t streams = 0;
-  uint32_t run = block_excl_scan32(mine, s_red, &streams);
-  const uint64_t C = kAnsFixed + 4ull * K + streams;
-  const bool coded = C < E;
-  if (coded) {
-    uint8_t *sec = enc + exc_offset(n, a.log2B);
-    uint32_t *ends = reinterpret_cast<uint32_t *>(sec + kAnsFixed);
-    for (uint32_t c = k0; c < k1; ++c) {
-      run += (256u + 2u * a.counts[c] + 3u) & ~3u;
-      ends[c] = run;
-    }
-    reinterpret_cast<uint16_t *>(sec + 8)[tid] = uint16_t(a.ans->freq[tid]);
-    if (tid == 0) {
-      reinterpret_cast<uint32_t *>(sec)[0] = K;
-      reinterpret_cast<uint32_t *>(sec)[1] = kAnsChunk;
-      const uint64_t total = kHeaderBytes + pad16(n) + pad16(bm) + pad16(C);
-      reinterpret_cast<uint32_t *>(enc)[1] = kVersion | (kModeAns << 16);
-      reinterpret_cast<uint64_t *>(enc)[5] = n + bm + C;
-      reinterpret_cast<uint64_t *>(enc)[6] = total;
-      if (a.out_bytes) *a.out_bytes = total;
-    }
-  } else if (tid == 0 && a.out_bytes) {
-    *a.out_bytes = old_total;
+  const uint32_t per = (K + gridDim.x - 1) / gridDim.x;
+  const uint32_t k0 = min(blockIdx.x * per, K), k1 = min(k0 + per, K);
+  if (k0 == k1 && blockIdx.x) return;
+  uint32_t front = 0, all = 0;  // stream bytes in front of k0, and in all
+#pragma unroll 8
+  for (uint32_t c = tid; c < K; c += kThreads) {
+    const uint32_t b = stream_bytes(a.counts[c]);
+    all += b;
+    front += c < k0 ? b : 0u;
   }
-  if (tid == 0) a.ans->coded = coded ? 1u : 0u;
+  all = block_sum32<NW>(all, s_red);
+  front = block_sum32<NW>(front, s_red);
+  const uint64_t E = ld64(a.enc + 32);
+  const uint64_t C = kAnsFixed + 4ull * K + all;
+  if (C >= E) {
+    if (blockIdx.x == 0 && tid == 0 && a.out_bytes)
+      *a.out_bytes = ld64(a.enc + 48);
+    return;
+  }
+  uint8_t *const sec = a.enc + exc_offset(a.n, a.log2B);
+  uint32_t *const ends = reinterpret_cast<uint32_t *>(sec + kAnsFixed);
+  if (blockIdx.x == 0) put_section(a, K, sec, C, a.ans->freq[tid]);
+  for (uint32_t r0 = k0; r0 < k1; r0 += kThreads) {
+    const uint32_t c = r0 + tid;
+    const uint32_t b = c < k1 ? stream_bytes(a.counts[c]) : 0u;
+    uint32_t sum = 0;
+    const uint32_t at = front + block_excl_scan32<NW>(b, s_red, &sum);
+    s_start[tid] = at;
+    if (c < k1) ends[c] = at + b;
+    front += sum;
+    if (tid == 0) s_start[kThreads] = front;
+    __syncthreads();
+    for (uint32_t i = wave; i < kThreads && r0 + i < k1; i += NW)
+      copy_chunk(a, r0 + i, K, sec, s_start[i], s_start[i + 1],
+                 a.counts[r0 + i]);
+    __syncthreads();
+  }
 }
 
-__global__ __launch_bounds__(kThreads) void ans_copy_kernel(AnsEncArgs a) {
-  if (!a.ans->coded) return;
-  const uint32_t K = a.ans->K;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint8_t *sec = a.enc + exc_offset(a.n, a.log2B);
-  const uint32_t *ends = reinterpret_cast<const uint32_t *>(sec + kAnsFixed);
-  uint8_t *streams = sec + kAnsFixed + 4ull * K;
-  for (uint32_t c = blockIdx.x * kWaves + wave; c < K;
-       c += gridDim.x * kWaves) {
-    const uint32_t start = c ? ends[c - 1] : 0u;
-    uint8_t *dst = streams + start;
-    reinterpret_cast<uint32_t *>(dst)[lane] =
-        a.states[uint64_t(c) * 64 + uint32_t(lane)];
-    const uint32_t w = a.counts[c];
-    const uint16_t *src = a.words + uint64_t(c) * kAnsChunk + (kAnsChunk - w);
-    uint16_t *d16 = reinterpret_cast<uint16_t *>(dst + 256);
-    for (uint32_t k = uint32_t(lane); k < w; k += 64) d16[k] = src[k];
-    if ((w & 1u) && lane == 0) d16[w] = 0;
-    if (c == K - 1) {
-      // zero the section's padding up to 16 bytes
-      const uint64_t C = kAnsFixed + 4ull * K + ends[c];
-      for (uint64_t b = C + uint64_t(lane); b < pad16(C); b += 64) sec[b] = 0;
-    }
+// All of it for shards of up to kAnsSmallChunks chunks, a wave a chunk.
+constexpr uint32_t kAnsSmallChunks = 16;
+__global__ __launch_bounds__(64 * kAnsSmallChunks) void ans_code_small_kernel(
+    AnsEncArgs a) {
+  constexpr int NW = int(kAnsSmallChunks);
+  __shared__ uint4 s_tab[256];
+  __shared__ __align__(16) uint8_t s_sym[NW][kAnsChunk];
+  __shared__ TableScratch s_t;
+  __shared__ uint32_t s_words[NW];
+  const uint32_t tid = threadIdx.x;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t E = ans_to_code(a);
+  const uint32_t K = uint32_t((E + kAnsChunk - 1) / kAnsChunk);
+  if (K == 0) {
+    if (tid == 0 && a.out_bytes) *a.out_bytes = ld64(a.enc + 48);
+    return;
+  }
+  uint8_t *const sec = a.enc + exc_offset(a.n, a.log2B);
+  uint32_t *const s_h = reinterpret_cast<uint32_t *>(&s_sym[0][0]);
+  static_assert(sizeof(s_sym) >= 4 * kHistCopies * kHistStride, "histogram");
+  for (uint32_t i = tid; i < kHistCopies * kHistStride; i += 64 * NW)
+    s_h[i] = 0u;
+  __syncthreads();
+  hist_bytes(sec, E, uint64_t(tid) * 16, uint64_t(64 * NW) * 16, s_h);
+  __syncthreads();
+  uint32_t h = 0, cum;
+  if (tid < 256)
+    for (int c = 0; c < kHistCopies; ++c) h += s_h[c * kHistStride + tid];
+  const uint32_t f = quantise<NW>(h, E, &cum, s_t);
+  if (tid < 256) s_tab[tid] = coding_entry(f, cum);
+  __syncthreads();
+  const uint32_t words =
+      wave < K ? code_chunk(a, wave, sec, E, s_tab, s_sym[wave]) : 0u;
+  if ((tid & 63) == 0) s_words[wave] = words;
+  __syncthreads();  // and every symbol has been read
+  uint32_t start = 0, all = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < uint32_t(NW); ++w) {
+    const uint32_t b = w < K ? stream_bytes(s_words[w]) : 0u;
+    start += w < wave ? b : 0u;
+    all += b;
+  }
+  const uint64_t C = kAnsFixed + 4ull * K + all;
+  if (C >= E) {
+    if (tid == 0 && a.out_bytes) *a.out_bytes = ld64(a.enc + 48);
+    return;
+  }
+  put_section(a, K, sec, C, f);
+  if (wave < K) {
+    const uint32_t end = start + stream_bytes(words);
+    if ((tid & 63) == 0)
+      reinterpret_cast<uint32_t *>(sec + kAnsFixed)[wave] = end;
+    copy_chunk(a, wave, K, sec, start, end, words);
   }
 }
 
 // ============================================================== decoding ==
 
+// A wave's chunk stream in LDS: up to kAnsStage bytes of words are staged
+// whole, longer ones (over 6 bits a symbol) go through a ring of two 256-byte
+// blocks in the same place.
+constexpr uint32_t kAnsStage = 3072;
+
 // Grid (workgroups per shard, shards). A workgroup checks its shard's coded
-// section and builds the slot table (symbol | (f - 1) << 8 | (slot - cum)
-// << 20) in LDS; then every wave decodes chunks on its own (no further
-// barrier). A wave keeps a window of its stream's words in a ring of two
-// 128-word blocks in LDS (each lane writes words 2l and 2l + 1 of a block);
-// the words a step needs lie in that window and each lane that renormalises
-// reads its own, and the next block is loaded ahead into a register and
-// written over the block the window leaves. Any inconsistency sets
-// CIERA_DEVERR_FORMAT; every access stays inside the section and the shard's
-// exception list.
+// section and builds the slot table in LDS; then every wave decodes chunks on
+// its own (no further barrier). Any inconsistency sets CIERA_DEVERR_FORMAT;
+// every access stays inside the section and the shard's exception list.
+//
+// Bound by the instructions of a step (64 symbols, one per lane), not by
+// bandwidth: a step is 11 VALU, 2 LDS and 1 store. A slot's entry is
+// symbol | (f mod 4096) << 8 | (slot - cum) << 20, so the next state is one
+// multiply-add of two extracted fields; the one shard that f = 4096 leaves
+// out, with a single symbol, never moves its states and is filled instead. A
+// chunk's words are staged in LDS whole, so a step only adds the words it used
+// to the count: no window to slide and no load to wait for behind the byte
+// stores. OLMoE layer, 16 shards (161 M symbols): 78 us, against 98 with the
+// words in a ring of two blocks, f - 1 in the entry (17 VALU a step) and the
+// slots' symbols found by binary search.
 template <int NT>
 __global__ __launch_bounds__(NT) void ans_decode_kernel(DecArgs a) {
   constexpr int NW = NT / 64;
   static_assert(NT >= 256 && NT % 256 == 0, "a thread per symbol at least");
-  __shared__ uint32_t s_slot[kAnsM];
+  constexpr uint32_t kLoads = kAnsStage / 256;  // dwords a lane, whole chunk
+  constexpr uint32_t kUnroll = 8;               // steps per loop iteration
+  // the waves' streams, then the slot table: a bad stream makes its wave read
+  // at most 64 * 64 words on from its start, which is still in here
+  __shared__ __align__(16) uint32_t s_mem[NW * kAnsStage / 4 + kAnsM];
+  uint32_t *const s_slot = s_mem + NW * kAnsStage / 4;
+  static_assert(kAnsM * 4 + kAnsStage >= (kAnsChunk + 64) * 2, "stays inside");
   __shared__ uint32_t s_freq[256];
   __shared__ uint32_t s_cum[256];
   __shared__ uint32_t s_red[4];
-  __shared__ uint32_t s_ring[NW][128];  // two blocks of 128 words a wave
+  __shared__ uint32_t s_top[NW];
   const uint32_t j = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
   // wave-uniform, so that the chunk loop and its lengths stay scalar
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint32_t *const ring = s_ring[wave];
-  const uint16_t *const ring16 = reinterpret_cast<const uint16_t *>(ring);
+  uint32_t *const words32 = s_mem + wave * int(kAnsStage / 4);
+  const uint16_t *const words16 = reinterpret_cast<const uint16_t *>(words32);
   const uint64_t off = a.offsets ? a.offsets[j] : 0ull;
   // the decode kernel reports a misplaced shard
   if ((off & 15ull) || off > a.bytes || a.bytes - off < kHeaderBytes) return;
@@ -428,19 +615,60 @@ __global__ __launch_bounds__(NT) void ans_decode_kernel(DecArgs a) {
     return;
   }
   __syncthreads();
-  for (uint32_t slot = uint32_t(tid); slot < kAnsM; slot += NT) {
-    uint32_t lo = 0, hi = 255;  // largest s with cum[s] <= slot
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi + 1) >> 1;
-      if (s_cum[mid] <= slot) lo = mid; else hi = mid - 1;
-    }
-    s_slot[slot] = lo | ((s_freq[lo] - 1u) << 8) | ((slot - s_cum[lo]) << 20);
-  }
+  // the symbol of every slot: symbol + 1 at each run's first slot, then a
+  // running maximum over the slots, kPer consecutive ones a thread (a binary
+  // search a slot over the prefix sums took a third of the kernel's time)
+  constexpr uint32_t kPer = kAnsM / NT;
+  static_assert(kPer % 4 == 0, "whole 16-byte vectors a thread");
+  uint4 *const mine = reinterpret_cast<uint4 *>(s_slot) + tid * (kPer / 4);
+#pragma unroll
+  for (uint32_t q = 0; q < kPer / 4; ++q) mine[q] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
+  if (tid < 256 && f) s_slot[before + inc - f] = uint32_t(tid) + 1u;
+  __syncthreads();
+  uint32_t sym[kPer];
+#pragma unroll
+  for (uint32_t q = 0; q < kPer / 4; ++q) {
+    const uint4 v = mine[q];
+    sym[4 * q] = v.x;
+    sym[4 * q + 1] = v.y;
+    sym[4 * q + 2] = v.z;
+    sym[4 * q + 3] = v.w;
+  }
+#pragma unroll
+  for (uint32_t q = 1; q < kPer; ++q) sym[q] = max(sym[q], sym[q - 1]);
+  uint32_t top = sym[kPer - 1];  // the maximum up to this thread, in its wave
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t t = __shfl_up(top, d, 64);
+    if (lane >= d) top = max(top, t);
+  }
+  if (lane == 63) s_top[wave] = top;
+  __syncthreads();
+  uint32_t front = __shfl_up(top, 1, 64);
+  if (lane == 0) front = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w)
+    if (w < wave) front = max(front, s_top[w]);
+#pragma unroll
+  for (uint32_t q = 0; q < kPer; ++q) {
+    const uint32_t s = max(sym[q], front) - 1u;
+    const uint32_t slot = uint32_t(tid) * kPer + q;
+    sym[q] = s | ((s_freq[s] & (kAnsM - 1u)) << 8) | ((slot - s_cum[s]) << 20);
+  }
+#pragma unroll
+  for (uint32_t q = 0; q < kPer / 4; ++q)
+    mine[q] = make_uint4(sym[4 * q], sym[4 * q + 1], sym[4 * q + 2],
+                         sym[4 * q + 3]);
+  __syncthreads();
+  // f = 4096: the only symbol, in every slot
+  const uint32_t only = __builtin_amdgcn_readfirstlane(s_slot[0] & 255u);
+  const bool single = s_freq[only] == kAnsM;
   const uint32_t *ends = reinterpret_cast<const uint32_t *>(sec + kAnsFixed);
   const uint8_t *streams = sec + kAnsFixed + 4ull * K;
   const uint64_t avail = C - kAnsFixed - 4ull * K;
   uint8_t *const list = a.ans_exc + uint64_t(j) * a.ans_stride;
+
   for (uint32_t c = blockIdx.x * NW + uint32_t(wave); c < K;
        c += gridDim.x * NW) {
     const uint32_t start = c ? ends[c - 1] : 0u;
@@ -454,57 +682,93 @@ __global__ __launch_bounds__(NT) void ans_decode_kernel(DecArgs a) {
     const uint32_t wbytes = end - start - 256u;  // words and padding
     const uint32_t nwords = wbytes / 2u;
     const uint8_t *wsrc = st + 256;
+    // block b of the words: 256 bytes, a dword a lane
     auto block = [&](uint32_t b) -> uint32_t {
       const uint32_t o = b * 256u + 4u * uint32_t(lane);
       return o < wbytes ? ld32(wsrc + o) : 0u;
     };
     uint32_t x = ld32(st + 4u * uint32_t(lane));
-    __builtin_amdgcn_wave_barrier();  // the previous chunk's reads are done
-    ring[lane] = block(0);
-    ring[64 + lane] = block(1);
-    uint32_t pre = block(2);      // the block after the window
-    uint32_t next = 3, base = 0;  // word index of the window's first word
-    __builtin_amdgcn_wave_barrier();
-    bool bad = x < kAnsL;
-    uint32_t rd = 0;
+    {
+      uint32_t w[kLoads];
+#pragma unroll
+      for (uint32_t q = 0; q < kLoads; ++q) w[q] = block(q);
+      __builtin_amdgcn_wave_barrier();  // the previous chunk's reads are done
+#pragma unroll
+      for (uint32_t q = 0; q < kLoads; ++q) words32[q * 64 + lane] = w[q];
+      __builtin_amdgcn_wave_barrier();
+    }
     const uint64_t lo = uint64_t(c) * kAnsChunk;
     const uint32_t len = uint32_t(E - lo < kAnsChunk ? E - lo : kAnsChunk);
     uint8_t *dst = list + lo;
+    bool bad = x < kAnsL;
+    uint32_t rd = 0;
     // 64 symbols a step, one per lane; only the last step of the last chunk
     // can be partial (TAIL)
+    auto state = [&](uint32_t e) {
+      return __umul24((e >> 8) & (kAnsM - 1u), x >> kAnsScale) + (e >> 20);
+    };
     auto step = [&](uint32_t t, auto tail) {
       constexpr bool TAIL = decltype(tail)::value;
       const uint32_t i = t * 64 + uint32_t(lane);
       const bool live = !TAIL || i < len;
       const uint32_t e = s_slot[x & (kAnsM - 1u)];
-      const uint32_t xd =
-          (((e >> 8) & 0xFFFu) + 1u) * (x >> kAnsScale) + (e >> 20);
+      const uint32_t xd = state(e);
       if (live) dst[i] = uint8_t(e);
       x = live ? xd : x;
       const bool need = live && x < kAnsL;
       const uint64_t m = __ballot(need);
-      // the lane's word relative to the window (< 192: rd - base < 128),
-      // counted by mbcnt on top of rd - base
-      const uint32_t rel = __builtin_amdgcn_mbcnt_hi(
-          uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), rd - base));
-      // word base + rel of the stream sits at (base + rel) mod 256 of the ring
-      // a lane that reads past the stream's last word takes a word of
-      // padding or of the next block, and the check after the chunk fails
-      const uint32_t w = ring16[(base + rel) & 255u];
+      // word rd + (needing lanes below); past a bad stream's end some other
+      // LDS of this block is read, and the check after the chunk fails
+      const uint32_t w = words16[rd + lanes_below(m)];
+      x = need ? ((x << 16) | w) : x;
+      rd += uint32_t(__popcll(m));
+    };
+    // the same with the words in a ring of two blocks of 128 words: the next
+    // block is loaded ahead into a register and written over the one that the
+    // window leaves
+    uint32_t base = 0, next = 3, pre = 0;  // base: the window's first word
+    auto ring_step = [&](uint32_t t, auto tail) {
+      constexpr bool TAIL = decltype(tail)::value;
+      const uint32_t i = t * 64 + uint32_t(lane);
+      const bool live = !TAIL || i < len;
+      const uint32_t e = s_slot[x & (kAnsM - 1u)];
+      const uint32_t xd = state(e);
+      if (live) dst[i] = uint8_t(e);
+      x = live ? xd : x;
+      const bool need = live && x < kAnsL;
+      const uint64_t m = __ballot(need);
+      // word w of the stream sits at w mod 256 of the ring (rd - base < 128)
+      const uint32_t w = words16[(rd + lanes_below(m)) & 255u];
       x = need ? ((x << 16) | w) : x;
       rd += uint32_t(__popcll(m));
       if (rd - base >= 128u) {  // uniform: slide the window by one block
         __builtin_amdgcn_wave_barrier();
-        ring[((base >> 7) & 1u) * 64u + uint32_t(lane)] = pre;
+        words32[((base >> 7) & 1u) * 64u + uint32_t(lane)] = pre;
         __builtin_amdgcn_wave_barrier();
         pre = block(next++);
         base += 128u;
       }
     };
     const uint32_t full = len / 64;
-    for (uint32_t t = 0; t < full; ++t)
-      step(t, std::integral_constant<bool, false>{});
-    if (len % 64) step(full, std::integral_constant<bool, true>{});
+    if (single) {
+      for (uint32_t i = uint32_t(lane); i < len; i += 64)
+        dst[i] = uint8_t(only);
+    } else if (wbytes <= kAnsStage) {
+      uint32_t t = 0;
+      for (; t + kUnroll <= full; t += kUnroll) {
+#pragma unroll
+        for (uint32_t u = 0; u < kUnroll; ++u)
+          step(t + u, std::integral_constant<bool, false>{});
+      }
+      for (; t < full; ++t) step(t, std::integral_constant<bool, false>{});
+      if (len % 64) step(full, std::integral_constant<bool, true>{});
+    } else {
+      pre = block(2);
+#pragma unroll 1
+      for (uint32_t t = 0; t < full; ++t)
+        ring_step(t, std::integral_constant<bool, false>{});
+      if (len % 64) ring_step(full, std::integral_constant<bool, true>{});
+    }
     // every state back at L, the words used up exactly (none read past the
     // stream's end), only zero padding after
     bad = bad || x != kAnsL;
@@ -521,17 +785,19 @@ __global__ __launch_bounds__(NT) void ans_decode_kernel(DecArgs a) {
 
 hipError_t launch_ans_code(const AnsEncArgs &a, hipStream_t s) {
   if (a.kmax == 0) return hipSuccess;
-  hipError_t e = launch_fill_zero(a.ans, sizeof(AnsCtl), s);
-  if (e != hipSuccess) return e;
-  const uint32_t g = a.kmax / 4 + 1 < 1024u ? a.kmax / 4 + 1 : 1024u;
-  // every histogram workgroup adds its bins to the same few hot counters at
-  // the end: 256 workgroups measured 15.3 us against 19.3 us for 1024
-  const uint32_t gh = g < 256u ? g : 256u;
-  hipLaunchKernelGGL(ans_hist_kernel, dim3(gh), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(ans_table_kernel, dim3(1), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(ans_encode_kernel, dim3(g), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(ans_finalize_kernel, dim3(1), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(ans_copy_kernel, dim3(g), dim3(kThreads), 0, s, a);
+  if (a.kmax <= kAnsSmallChunks) {
+    hipLaunchKernelGGL(ans_code_small_kernel, dim3(1),
+                       dim3(64 * kAnsSmallChunks), 0, s, a);
+    return hipGetLastError();
+  }
+  const uint32_t rows = std::min(a.kmax / 4 + 1, kHistRows);
+  const uint32_t g =
+      std::min((a.kmax + kCodeWaves - 1) / kCodeWaves, uint32_t(512));
+  hipLaunchKernelGGL(ans_hist_kernel, dim3(rows), dim3(kHistThreads), 0, s, a);
+  hipLaunchKernelGGL(ans_encode_kernel, dim3(g), dim3(kCodeThreads), 0, s, a,
+                     rows);
+  hipLaunchKernelGGL(ans_copy_kernel, dim3(std::min(a.kmax / 4 + 1, 1024u)),
+                     dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -198,12 +198,9 @@ inline uint64_t dec_ws_bytes(uint64_t n, uint32_t nshards) {
 // The area starts at ans_ws_offset(n, B, nshards), past everything else the
 // calls use.
 struct AnsCtl {
-  uint32_t hist[256];  // exception byte counts
   uint32_t freq[256];  // quantised frequencies (sum kAnsM)
-  uint32_t cum[256];   // their exclusive prefix sums
   uint32_t K;          // chunks of the shard being coded
-  uint32_t coded;      // 1 when the coded section replaced the raw one
-  uint32_t reserved[254];
+  uint32_t reserved[767];
 };
 static_assert(sizeof(AnsCtl) == 4096, "rANS control block is 4 KB");
 constexpr int kAnsMinLog2B = 4;  // rANS-coded sections need B >= 16

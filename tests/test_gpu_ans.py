@@ -203,3 +203,44 @@ def test_ans_code_is_deterministic_and_idempotent(gu, orc):
     torch.cuda.synchronize()
     assert int(nbytes.item()) == ta
     np.testing.assert_array_equal(gu.host_u8(buf)[:ta], a)
+
+
+@pytest.mark.parametrize("n", [5, 4096, 65_535, 65_536, 65_537, 69_632,
+                               131_071, 1_000_001])
+@pytest.mark.parametrize("kind", ["one", "two", "flat100", "mixed"])
+def test_ans_streams_of_every_length(gu, orc, n, kind):
+    """Both coders (one workgroup up to 65,536 values, three kernels above)
+    and both ways the decoder holds a chunk's words: a single symbol (no
+    word), two, 100 equally likely ones (6.6 bits each: more words than are
+    staged at once), and chunks of either sort side by side. Coded bytes,
+    decoded values and caches match the oracle."""
+    from paper_2609_04609_amd import ciera
+    rng = np.random.default_rng(n)
+    e = {"one": np.full(n, 77),
+         "two": rng.choice([60, 200], n, p=[0.999, 0.001]),
+         "flat100": rng.integers(50, 150, n),
+         "mixed": np.where((np.arange(n) // 8192) % 2 == 0,
+                           rng.integers(118, 122, n),
+                           rng.integers(20, 200, n))}[kind].astype(np.uint16)
+    w2h = ((rng.integers(0, 2, n).astype(np.uint16) << 15) | (e << 7)
+           | rng.integers(0, 128, n).astype(np.uint16))
+    B = 16
+    cache_h = (e ^ 1).astype(np.uint8)  # every block changed
+    ws = ciera.Workspace(n, 2, B, ans=True)
+    got, total = _gpu_coded(gu, gu.dev_bits(w2h), gu.dev_u8(cache_h), B, ws)
+    expect = orc.ans_code(orc.encode(w2h, cache_h, B), n)
+    assert total == expect.size
+    np.testing.assert_array_equal(got, expect)
+    if n > 8192:
+        assert orc.header(expect)["mode"] == 2
+    g, offs = gu.gather([expect, expect])
+    out = torch.zeros(2 * n, dtype=torch.int16, device="cuda")
+    cache = gu.dev_u8(np.concatenate([cache_h, cache_h]))
+    ciera.decode_gathered_t(gu.dev_u8(g),
+                            torch.from_numpy(offs.view(np.int64)).cuda(), n, B,
+                            out, cache, ws)
+    np.testing.assert_array_equal(gu.host_u16(out),
+                                  np.concatenate([w2h, w2h]))
+    np.testing.assert_array_equal(gu.host_u8(cache),
+                                  np.concatenate([e, e]).astype(np.uint8))
+    assert ws.error() == 0
