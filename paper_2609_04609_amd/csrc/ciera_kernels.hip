@@ -1465,7 +1465,9 @@ __global__ __launch_bounds__(kSmallThreads) void encode_small_kernel(
     exc_finish<ELEMS, F16>(a, carry, lane, s_last != 0);
 }
 
-// Raw form: header + the values unchanged. One octet per lane.
+// Raw form: header + the values unchanged. One octet per lane, non-temporal:
+// 26.2M values, with the decode of that shard, take 43.9 us against 49.5 with
+// plain accesses.
 __global__ __launch_bounds__(kThreads) void encode_raw_kernel(
     const uint16_t *w, uint64_t n, uint32_t B, uint8_t *out,
     uint64_t *out_bytes, uint32_t dtype) {
@@ -1476,7 +1478,10 @@ __global__ __launch_bounds__(kThreads) void encode_raw_kernel(
   if (o < octets) {
     const uint64_t elem = o * 8;
     const uint32_t valid = octet_valid(elem, n);
-    store_w8(body + elem, load_w8(w + elem, valid), valid);
+    if (valid == 8)
+      st_nt16(body + elem, ld_nt16(w + elem));
+    else
+      store_w8(body + elem, load_w8(w + elem, valid), valid);
   }
   if (blockIdx.x == 0) {
     const uint32_t tid = threadIdx.x;
@@ -1675,13 +1680,19 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
   uint16_t *const out = UPDATE_ONLY ? nullptr : a.out + uint64_t(j) * n;
 
   if (sv.mode == kModeRaw) {
+    // three streams touched once, non-temporal as in the merge: 16 shards of
+    // 26.2M values decode in 374 us (encode of one included) against 395 with
+    // plain accesses, of 1.06M values in 20.0 against 23.5; plain loads under
+    // non-temporal stores win while the gather fits the Infinity Cache from
+    // one call to the next (19.4 us), and lose beyond (389)
     const uint16_t *body =
         reinterpret_cast<const uint16_t *>(sv.enc + kHeaderBytes);
     if (full) {
       uint4 wv[OCT];
 #pragma unroll
       for (int u = 0; u < OCT; ++u)
-        wv[u] = ld16(body + base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+        wv[u] = ld_nt16(body + base +
+                        (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
 #pragma unroll
       for (int u = 0; u < OCT; ++u) {
         const uint64_t elem =
@@ -1694,8 +1705,8 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
           split4(wv[u].x, wv[u].y, e.x, sm.x);
           split4(wv[u].z, wv[u].w, e.y, sm.y);
         }
-        if (!UPDATE_ONLY) st16(out + elem, wv[u]);
-        st8(cache + elem, e);
+        if (!UPDATE_ONLY) st_nt16(out + elem, wv[u]);
+        st_nt8(cache + elem, e);
       }
       return;
     }
@@ -1982,6 +1993,51 @@ __global__ __launch_bounds__(kThreads) void count_tile_bits_kernel(
   if (lane == 0) a.tile_excl[uint64_t(j) * dec_count_stride(tiles) + t] = c;
 }
 
+// A tile of a raw shard in the B = 1 decode: the values copied, their
+// exponents to the cache, as in decode_kernel (which keeps the code in place:
+// with a call here it takes 81 instead of 72 VGPRs and 2% longer on every
+// layer). 16 raw shards of 1.06M values: 21.8 us against 25.3 octet by octet.
+template <int OCT, bool UPDATE_ONLY>
+__device__ __forceinline__ void decode_raw_tile(const ShardView &sv,
+                                                uint64_t base, uint64_t n,
+                                                bool full, int wave, int lane,
+                                                uint8_t *cache,
+                                                uint16_t *out) {
+  const uint16_t *body =
+      reinterpret_cast<const uint16_t *>(sv.enc + kHeaderBytes);
+  if (full) {
+    uint4 wv[OCT];
+#pragma unroll
+    for (int u = 0; u < OCT; ++u)
+      wv[u] = ld_nt16(body + base +
+                      (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+#pragma unroll
+    for (int u = 0; u < OCT; ++u) {
+      const uint64_t elem =
+          base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u;
+      uint2 e, sm;
+      split4(wv[u].x, wv[u].y, e.x, sm.x);
+      split4(wv[u].z, wv[u].w, e.y, sm.y);
+      if (!UPDATE_ONLY) st_nt16(out + elem, wv[u]);
+      st_nt8(cache + elem, e);
+    }
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < OCT; ++u) {
+    const uint32_t o = uint32_t(wave * OCT + u) * 64u + lane;
+    const uint64_t elem = base + uint64_t(o) * 8u;
+    const uint32_t valid = octet_valid(elem, n);
+    if (!valid) continue;
+    const uint4 wv = load_w8(body + elem, valid);
+    uint2 e, sm;
+    split4(wv.x, wv.y, e.x, sm.x);
+    split4(wv.z, wv.w, e.y, sm.y);
+    if (!UPDATE_ONLY) store_w8(out + elem, wv, valid);
+    store_b8(cache + elem, e, valid);
+  }
+}
+
 // Decode, B = 1, step 2 (step 3 after a scan of the counts): patch and merge
 // (UPDATE_ONLY: patch only).
 template <int OCT, bool UPDATE_ONLY>
@@ -2002,20 +2058,8 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
   uint16_t *const out = UPDATE_ONLY ? nullptr : a.out + uint64_t(j) * n;
 
   if (sv.mode == kModeRaw) {
-    const uint16_t *body =
-        reinterpret_cast<const uint16_t *>(sv.enc + kHeaderBytes);
-#pragma unroll
-    for (int u = 0; u < OCT; ++u) {
-      const uint64_t elem = base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u;
-      const uint32_t valid = octet_valid(elem, n);
-      if (!valid) continue;
-      const uint4 wv = load_w8(body + elem, valid);
-      uint2 e, sm;
-      split4(wv.x, wv.y, e.x, sm.x);
-      split4(wv.z, wv.w, e.y, sm.y);
-      if (!UPDATE_ONLY) store_w8(out + elem, wv, valid);
-      store_b8(cache + elem, e, valid);
-    }
+    decode_raw_tile<OCT, UPDATE_ONLY>(sv, base, n, base + T <= n, wave, lane,
+                                      cache, out);
     return;
   }
 
