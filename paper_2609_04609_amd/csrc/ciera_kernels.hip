@@ -25,6 +25,8 @@
 //            list costs one re-read of the changed blocks (1 or 2 bytes per
 //            changed value) instead of a cross-workgroup scan whose waits
 //            would hold every tile's slot behind its slowest predecessor.
+//            Small shards take encode_small_kernel instead: one workgroup, one
+//            launch.
 //   decode   for all R gathered shards at once: ExpCache patch + Merge. Each
 //            tile finds its first exception by counting the bitmap bits in
 //            front of it (the bitmap is 1/(8B) of the shard and stays in L2),
