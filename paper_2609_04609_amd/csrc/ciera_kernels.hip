@@ -1349,7 +1349,6 @@ __global__ __launch_bounds__(kSmallThreads) void encode_small_kernel(
   uint8_t *const bmp_out = sm_out + n16;
   uint8_t *const exc_out = bmp_out + bm16;
   uint32_t carry = 0;  // changed blocks (B = 1: values) of the rounds before
-  if (threadIdx.x == 0) s_last = 0;
   for (uint32_t t0 = 0; t0 < a.num_tiles; t0 += W) {
     // opaque to the compiler in every round: it would otherwise keep what it
     // derives from the lane in registers across rounds (128 VGPRs and scratch)
@@ -1386,10 +1385,11 @@ __global__ __launch_bounds__(kSmallThreads) void encode_small_kernel(
         } else if (lane == 0) {
           s_bits[wave] = uint32_t(fw[0]);
         }
-        // the last block's flag decides the list's length
-        const uint64_t lb = blocks_of(n, log2B) - 1;
-        if (n && tile == a.num_tiles - 1 && lane == 0) {
-          const uint32_t k = uint32_t(lb - (cbase >> log2B));
+        // the last block's flag decides the list's length; no other wave
+        // writes it (n = 0: no flag is set)
+        if (tile == a.num_tiles - 1 && lane == 0) {
+          const uint32_t k =
+              n ? uint32_t(blocks_of(n, log2B) - 1 - (cbase >> log2B)) : 0u;
           s_last = uint32_t(pick<4>(fw, k >> 6) >> (k & 63u)) & 1u;
         }
       }
@@ -1464,7 +1464,7 @@ __global__ __launch_bounds__(kSmallThreads) void encode_small_kernel(
     __syncthreads();  // s_cnt and s_bits are read, s_last is written
   }
   if (wave == 0)
-    exc_finish<ELEMS, F16>(a, carry, lane, s_last != 0);
+    exc_finish<ELEMS, F16>(a, carry, lane, !ELEMS && s_last != 0);
 }
 
 // Raw form: header + the values unchanged. One octet per lane, non-temporal:
