@@ -3,6 +3,9 @@ and descending order between barriers, and workgroups likewise, encodes,
 decodes and rANS coding match the oracle byte for byte. What one order writes
 over another's result is a missing barrier. Runs on the CPU (tests/host_wave.py);
 no kernel here depends on the values' distribution, so small shards do."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -121,3 +124,25 @@ def test_rans(host, orc, n):
         np.testing.assert_array_equal(got, np.concatenate([w, w]), err_msg=msg)
         np.testing.assert_array_equal(c, np.concatenate([e, e]), err_msg=msg)
         assert host.error(ws) == 0, msg
+
+
+def test_rans_size_decision_near_2_32(tmp_path):
+    """A list of 2^32 - 256 bytes in K chunks: its streams are coded only if
+    all of them together are shorter, also where their sum passes 2^32."""
+    exe = hw.compile_exe(os.path.join(hw.HERE, "native", "ans_total.cpp"),
+                         str(tmp_path / "ans_total"))
+    n, K = (1 << 32) - 256, 1 << 20
+    # 8 bits a symbol (2,048 words) and more; 1,919 make the streams 2^32 bytes,
+    # 1,918 the whole section more than that, 1,916 less than the list
+    words = [2048, 2100, 3136, 1920, 1919, 1918, 1916, 1000]
+    r = subprocess.run([exe, *map(str, words)], capture_output=True, text=True,
+                       check=True, timeout=300)
+    rows = [tuple(map(int, line.split())) for line in r.stdout.splitlines()]
+    assert len(rows) == len(words)
+    front = 64 + n + (1 << 20)  # header, values, bitmap (of n / 512 blocks)
+    for w, (mode, total) in zip(words, rows):
+        coded = 520 + 4 * K + K * ((256 + 2 * w + 3) // 4 * 4)
+        if coded < n:
+            assert (mode, total) == (2, front + (coded + 15) // 16 * 16), w
+        else:
+            assert (mode, total) == (0, front + n), w
