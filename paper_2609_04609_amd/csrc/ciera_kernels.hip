@@ -2041,8 +2041,9 @@ __device__ __forceinline__ void decode_raw_tile(const ShardView &sv,
 }
 
 // Decode, B = 1, step 2 (step 3 after a scan of the counts): patch and merge
-// (UPDATE_ONLY: patch only).
-template <int OCT, bool UPDATE_ONLY>
+// (UPDATE_ONLY: patch only; SMALL: the only step, the tile counts the bitmap
+// in front of it).
+template <int OCT, bool UPDATE_ONLY, bool SMALL>
 __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
   constexpr uint32_t T = kThreads * 8 * OCT;
   __shared__ uint32_t s_seg[4 * OCT + 1];
@@ -2098,7 +2099,7 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
   // layers, no count kernel), scanned, or the counts in front of it added up
   // here, the loads of either sum behind the tile's own
   uint32_t tile_first;
-  if constexpr (OCT != int(kDecOct)) {
+  if constexpr (SMALL) {
     tile_first = block_sum(popc_bytes_part<kGroupLoads>(bmp, base >> 3), s_red);
   } else {
     const uint32_t *const counts =
@@ -2303,18 +2304,18 @@ hipError_t launch_encode_raw(const uint16_t *w, uint64_t n, uint32_t B,
 }
 
 namespace {
-template <int OCT>
+template <int OCT, bool SMALL>
 void launch_decode_tiles(const DecArgs &a, hipStream_t s) {
   constexpr uint64_t T = uint64_t(kThreads) * 8 * OCT;
   const dim3 grid(uint32_t((a.n + T - 1) / T), a.nshards), block(kThreads);
   const bool upd = a.out == nullptr;
   if (a.log2B == 0) {
     if (upd)
-      hipLaunchKernelGGL((decode_elems_kernel<OCT, true>), grid, block, 0, s,
-                         a);
+      hipLaunchKernelGGL((decode_elems_kernel<OCT, true, SMALL>), grid, block,
+                         0, s, a);
     else
-      hipLaunchKernelGGL((decode_elems_kernel<OCT, false>), grid, block, 0, s,
-                         a);
+      hipLaunchKernelGGL((decode_elems_kernel<OCT, false, SMALL>), grid, block,
+                         0, s, a);
   } else if (a.f16) {
     if (upd)
       hipLaunchKernelGGL((decode_kernel<OCT, true, true>), grid, block, 0, s,
@@ -2335,7 +2336,7 @@ hipError_t launch_decode(const DecArgs &a, hipStream_t s) {
   const uint64_t tiles = dec_tiles(a.n);
   if (tiles == 0 || a.nshards == 0) return hipSuccess;
   if (dec_small(a.n, a.nshards, a.log2B)) {
-    launch_decode_tiles<int(kDecOctSmall)>(a, s);
+    launch_decode_tiles<int(kDecOctSmall), true>(a, s);
     return hipGetLastError();
   }
   if (a.log2B == 0) {
@@ -2350,7 +2351,7 @@ hipError_t launch_decode(const DecArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(tile_prefix_kernel, dim3(a.nshards), dim3(kScanThreads),
                        0, s, a);
   }
-  launch_decode_tiles<int(kDecOct)>(a, s);
+  launch_decode_tiles<int(kDecOct), false>(a, s);
   return hipGetLastError();
 }
 

@@ -78,11 +78,10 @@ def test_encode(host, orc, n, B):
 
 # small decode tiles (4096 values) and large ones, rANS below and above 16
 # chunks, one shard of the gather raw
-@pytest.mark.parametrize("n,R", [(4097, 3), (70_001, 2), (16_384, 256)])
-@pytest.mark.parametrize("B", [1, 64, 4096])
+@pytest.mark.parametrize("n,R,B", [
+    (4097, 3, 1), (4097, 3, 64), (4097, 3, 4096), (70_001, 2, 1),
+    (70_001, 2, 64), (70_001, 2, 4096), (16_384, 256, 1), (16_384, 256, 512)])
 def test_decode(host, orc, n, R, B):
-    if R > 8 and B == 64:
-        pytest.skip("one block size of many shards is enough")
     w, at = _weights(R * n, n + B)
     w2 = _before(w, at)
     cache = orc.split(w)[0]
@@ -146,3 +145,21 @@ def test_rans_size_decision_near_2_32(tmp_path):
             assert (mode, total) == (2, front + (coded + 15) // 16 * 16), w
         else:
             assert (mode, total) == (0, front + n), w
+
+
+def test_decode_of_builds_with_small_tiles(orc, tmp_path):
+    """Built with 2 octets a lane, where large and small tiles are the same
+    size, the decode at B = 1 still counts in front of its tiles."""
+    host = hw.HostLib(hw.compile_lib(str(tmp_path / "libciera.so"),
+                                     ["CIERA_DEC_OCT=2"]))
+    for n, R in ((20_001, 2), (70_001, 20)):  # under and over 256 tiles
+        w, at = _weights(R * n, n)
+        w2 = _before(w, at)
+        cache = orc.split(w)[0]
+        shards = [orc.encode(w2[j * n:(j + 1) * n], cache[j * n:(j + 1) * n], 1)
+                  for j in range(R)]
+        ws = host.workspace(n, R, 1)
+        ws[256:] = 0x5A  # what an earlier call may have left
+        np.testing.assert_array_equal(host.decode(shards, n, 1, cache, ws), w2)
+        np.testing.assert_array_equal(cache, orc.split(w2)[0])
+        assert host.error(ws) == 0
