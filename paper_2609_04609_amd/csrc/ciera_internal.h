@@ -78,7 +78,7 @@ static_assert((kDecTile & (kDecTile - 1)) == 0 && kDecTile >= 4096,
 // lane): whole blocks at every B.
 constexpr uint64_t kEncChunk = 4096;
 // Shards of up to this many values are encoded by one workgroup in one launch
-// (encode_small_kernel): 12 of its 16 waves' chunks. One CU needs 4.2 us for
+// (encode_small_kernel), a wave a chunk. One CU needs 4.2 us for
 // 128 values, 5.9 for 32,768 and 8.1 for 65,536, the two launches 5.4, 7.0 and
 // 7.0 (encodes back to back in a HIP graph, B = 512); with the block hash or in
 // fp16 a full round takes 9 to 10 us, and the lines cross at the same place.

@@ -1325,22 +1325,26 @@ __global__ __launch_bounds__(kThreads) void encode_exc_blocks_kernel(
 }
 
 // The whole encode of a small shard (up to kEncSmall values) in one launch of
-// one workgroup: 16 waves take a chunk each, put their counts together in LDS
-// and write their changed exponents from registers (more chunks than waves:
-// round after round with the running count). A second kernel, and the re-read of what it copies,
-// would cost more than the other CUs could save. Bound by latency: load,
-// compare, count across the waves, store (4.2 us at 128 values against 5.4 for
-// the two kernels, and one launch of 2.5 us less on the host).
-constexpr int kSmallThreads = 1024;
+// one workgroup, a wave a chunk: the waves put their counts together in LDS
+// and write their changed exponents from registers. A second kernel, and the
+// re-read of what it copies, would cost more than the other CUs could save.
+// Bound by latency: load, compare, count across the waves, store (3.7 us at 128
+// values against 5.4 for the two kernels, and one launch of 2.5 us less on the
+// host; 4.15 us with 16 waves whatever the shard and a loop over rounds).
+constexpr int kSmallWaves = int(kEncSmall / kEncChunk);
+static_assert(kEncSmall % kEncChunk == 0 && kSmallWaves >= 1 &&
+                  kSmallWaves <= 16,
+              "a wave a chunk in one workgroup");
 template <bool ELEMS, int DET, bool F16, bool BIG>
-__global__ __launch_bounds__(kSmallThreads) void encode_small_kernel(
+__global__ __launch_bounds__(64 * kSmallWaves) void encode_small_kernel(
     EncArgs a) {
-  constexpr uint32_t W = kSmallThreads / 64;
+  constexpr uint32_t W = kSmallWaves;
   __shared__ uint32_t s_cnt[W];
   __shared__ uint32_t s_bits[W];
   __shared__ uint32_t s_last;
-  uint32_t lane = threadIdx.x & 63;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t tile = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t nt = a.num_tiles;  // the workgroup's waves
   const uint64_t n = a.n;
   const uint32_t log2B = a.log2B;
   const uint64_t n16 = pad16(sm_bytes(n, F16));
@@ -1348,123 +1352,108 @@ __global__ __launch_bounds__(kSmallThreads) void encode_small_kernel(
   uint8_t *const sm_out = a.out + kHeaderBytes;
   uint8_t *const bmp_out = sm_out + n16;
   uint8_t *const exc_out = bmp_out + bm16;
-  uint32_t carry = 0;  // changed blocks (B = 1: values) of the rounds before
-  for (uint32_t t0 = 0; t0 < a.num_tiles; t0 += W) {
-    // opaque to the compiler in every round: it would otherwise keep what it
-    // derives from the lane in registers across rounds (128 VGPRs and scratch)
-    asm volatile("" : "+v"(lane));
-    const uint32_t tile = t0 + wave;
-    const bool live = tile < a.num_tiles;
-    const uint64_t cbase = uint64_t(tile) * kEncChunk;
-    uint32_t mask[8], excl[8], count = 0;
-    uint2 e[8];
-    uint64_t fw[4];
-    if (live) {
-      encode_chunk<ELEMS, DET, F16, true, BIG>(a, cbase, lane, sm_out, e, mask,
-                                               fw);
-      if (ELEMS) {
+  const uint64_t cbase = uint64_t(tile) * kEncChunk;
+  uint32_t mask[8], excl[8], count = 0;
+  uint2 e[8];
+  uint64_t fw[4];
+  encode_chunk<ELEMS, DET, F16, true, BIG>(a, cbase, lane, sm_out, e, mask,
+                                           fw);
+  if (ELEMS) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
-          if (elem < n) bmp_out[elem >> 3] = uint8_t(mask[u]);
-          const uint32_t c = __popc(mask[u]);
-          const uint32_t incl = wave_incl_scan(c);
-          excl[u] = count + incl - c;
-          count += __builtin_amdgcn_readlane(incl, 63);
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) count += uint32_t(__popcll(fw[k]));
-        const uint32_t nb = kEncChunk >> log2B;  // blocks in a chunk
-        if (!BIG) {
-          const uint64_t byte0 = uint64_t(tile) * (nb >> 3);
-          for (uint32_t i = lane; i < (nb >> 3); i += 64)
-            if (byte0 + i < bm16)
-              bmp_out[byte0 + i] =
-                  uint8_t(pick<4>(fw, i >> 3) >> ((i & 7u) * 8u));
-        } else if (lane == 0) {
-          s_bits[wave] = uint32_t(fw[0]);
-        }
-        // the last block's flag decides the list's length; no other wave
-        // writes it (n = 0: no flag is set)
-        if (tile == a.num_tiles - 1 && lane == 0) {
-          const uint32_t k =
-              n ? uint32_t(blocks_of(n, log2B) - 1 - (cbase >> log2B)) : 0u;
-          s_last = uint32_t(pick<4>(fw, k >> 6) >> (k & 63u)) & 1u;
-        }
-      }
-    } else if (BIG && lane == 0) {
-      s_bits[wave] = 0;
+    for (int u = 0; u < 8; ++u) {
+      const uint64_t elem = cbase + (uint64_t(u) * 64 + lane) * 8;
+      if (elem < n) bmp_out[elem >> 3] = uint8_t(mask[u]);
+      const uint32_t c = __popc(mask[u]);
+      const uint32_t incl = wave_incl_scan(c);
+      excl[u] = count + incl - c;
+      count += __builtin_amdgcn_readlane(incl, 63);
     }
-    if (lane == 0) s_cnt[wave] = count;
-    __syncthreads();
-    uint32_t before = carry, total = 0;
+  } else {
 #pragma unroll
-    for (uint32_t w = 0; w < W; ++w) {
-      const uint32_t c = s_cnt[w];
-      before += w < wave ? c : 0u;
-      total += c;
+    for (int k = 0; k < 4; ++k) count += uint32_t(__popcll(fw[k]));
+    const uint32_t nb = kEncChunk >> log2B;  // blocks in a chunk
+    if (!BIG) {
+      const uint64_t byte0 = uint64_t(tile) * (nb >> 3);
+      for (uint32_t i = lane; i < (nb >> 3); i += 64)
+        if (byte0 + i < bm16)
+          bmp_out[byte0 + i] =
+              uint8_t(pick<4>(fw, i >> 3) >> ((i & 7u) * 8u));
+    } else if (lane == 0) {
+      s_bits[tile] = uint32_t(fw[0]);
     }
-    carry += total;
-    if (BIG) {
-      // byte i of the round: the bits of 8 / nb chunks
-      const uint32_t nb_log2 = 12 - log2B, cpb_log2 = log2B - 9;
-      const uint64_t pos = (uint64_t(t0) >> cpb_log2) + threadIdx.x;
-      if (threadIdx.x < (W >> cpb_log2) && pos < bm16) {
-        uint32_t b = 0;
-        for (uint32_t i = 0; i < (1u << cpb_log2); ++i)
-          b |= s_bits[(threadIdx.x << cpb_log2) + i] << (i << nb_log2);
-        bmp_out[pos] = uint8_t(b);
-      }
+    // the last block's flag decides the list's length; no other wave writes
+    // it (n = 0: no flag is set)
+    if (tile == nt - 1 && lane == 0) {
+      const uint32_t k =
+          n ? uint32_t(blocks_of(n, log2B) - 1 - (cbase >> log2B)) : 0u;
+      s_last = uint32_t(pick<4>(fw, k >> 6) >> (k & 63u)) & 1u;
     }
-    if (live && ELEMS) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        uint32_t mm = mask[u], pos = before + excl[u];
-        while (mm) {
-          exc_out[pos++] = uint8_t(octet_byte(e[u], __builtin_ctz(mm)));
-          mm &= mm - 1u;
-        }
-      }
-    } else if (live) {
-      const uint32_t left =
-          uint32_t(min(n - cbase, uint64_t(kEncChunk)));  // values from cbase
-      uint32_t in_front[4];  // flags in the words in front of each
-      uint32_t run = before;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        in_front[k] = run;
-        run += uint32_t(__popcll(fw[k]));
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t rel = uint32_t(u) * 512u + lane * 8u;
-        const uint32_t b = rel >> log2B;
-        // a unit's blocks share one word of the flags
-        const uint32_t q = (uint32_t(u) * 512u >> log2B) >> 6;
-        const uint64_t word =
-            q == 0 ? fw[0] : q == 1 ? fw[1] : q == 2 ? fw[2] : fw[3];
-        const uint32_t front = q == 0   ? in_front[0]
-                               : q == 1 ? in_front[1]
-                               : q == 2 ? in_front[2]
-                                        : in_front[3];
-        // (no flag past n; the exponents past n in the last octet are 0, as
-        // the padding that they fall into)
-        if (rel < left && ((word >> (b & 63u)) & 1u)) {
-          const uint32_t rank =
-              front +
-              uint32_t(__popcll(word & ((1ull << (b & 63u)) - 1ull)));
-          put_exc_exps<F16>(exc_out,
-                            (rank << log2B) | (rel & ((1u << log2B) - 1u)),
-                            e[u], 8);
-        }
-      }
-    }
-    if (tile == a.num_tiles - 1) pad_sections<ELEMS, F16>(a, lane);
-    __syncthreads();  // s_cnt and s_bits are read, s_last is written
   }
-  if (wave == 0)
-    exc_finish<ELEMS, F16>(a, carry, lane, !ELEMS && s_last != 0);
+  if (lane == 0) s_cnt[tile] = count;
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < W; ++w) {
+    const uint32_t c = w < nt ? s_cnt[w] : 0u;
+    before += w < tile ? c : 0u;
+    total += c;
+  }
+  if (BIG) {
+    // bitmap byte i: the bits of 8 / nb chunks
+    const uint32_t nb_log2 = 12 - log2B, cpb_log2 = log2B - 9;
+    const uint32_t t0 = threadIdx.x << cpb_log2;
+    if (t0 < nt && threadIdx.x < bm16) {
+      uint32_t b = 0;
+      for (uint32_t i = 0; i < (1u << cpb_log2) && t0 + i < nt; ++i)
+        b |= s_bits[t0 + i] << (i << nb_log2);
+      bmp_out[threadIdx.x] = uint8_t(b);
+    }
+  }
+  if (ELEMS) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      uint32_t mm = mask[u], pos = before + excl[u];
+      while (mm) {
+        exc_out[pos++] = uint8_t(octet_byte(e[u], __builtin_ctz(mm)));
+        mm &= mm - 1u;
+      }
+    }
+  } else {
+    // values from cbase
+    const uint32_t left =
+        n > cbase ? uint32_t(min(n - cbase, uint64_t(kEncChunk))) : 0u;
+    uint32_t in_front[4];  // flags in the words in front of each
+    uint32_t run = before;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      in_front[k] = run;
+      run += uint32_t(__popcll(fw[k]));
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t rel = uint32_t(u) * 512u + lane * 8u;
+      const uint32_t b = rel >> log2B;
+      // a unit's blocks share one word of the flags
+      const uint32_t q = (uint32_t(u) * 512u >> log2B) >> 6;
+      const uint64_t word =
+          q == 0 ? fw[0] : q == 1 ? fw[1] : q == 2 ? fw[2] : fw[3];
+      const uint32_t front = q == 0   ? in_front[0]
+                             : q == 1 ? in_front[1]
+                             : q == 2 ? in_front[2]
+                                      : in_front[3];
+      // (no flag past n; the exponents past n in the last octet are 0, as
+      // the padding that they fall into)
+      if (rel < left && ((word >> (b & 63u)) & 1u)) {
+        const uint32_t rank =
+            front + uint32_t(__popcll(word & ((1ull << (b & 63u)) - 1ull)));
+        put_exc_exps<F16>(exc_out,
+                          (rank << log2B) | (rel & ((1u << log2B) - 1u)),
+                          e[u], 8);
+      }
+    }
+  }
+  if (tile == nt - 1) pad_sections<ELEMS, F16>(a, lane);
+  if (tile == 0) exc_finish<ELEMS, F16>(a, total, lane, !ELEMS && s_last != 0);
 }
 
 // Raw form: header + the values unchanged. One octet per lane, non-temporal:
@@ -2195,7 +2184,7 @@ hipError_t launch_encode_small(const EncArgs &a, hipStream_t s) {
                                             decltype(det)::value,
                                             decltype(f)::value,
                                             decltype(big)::value>),
-                       dim3(1), dim3(kSmallThreads), 0, s, a);
+                       dim3(1), dim3(64 * a.num_tiles), 0, s, a);
   };
   auto blocks = [&](auto det, auto f) {
     if (enc_class(a.log2B) == kInUnit)
