@@ -173,16 +173,30 @@ __host__ __device__ inline uint64_t dec_tiles(uint64_t n) {
 // Small layers: few tiles of 16384 values would leave CUs idle, so the decode
 // takes tiles of kDecOctSmall octets a lane. Every tile then counts the bitmap
 // in front of it, at B = 1 too (no count kernel), so that re-reading must stay
-// small as well. Two decodes from a HIP graph, 16384- against 4096-value
-// tiles: 16 shards of 8,192 values 14.4 / 6.8 us, of 131,072 (128 large tiles)
-// 11.1 / 10.8 us, in fp16 19.8 / 13.0, at B = 1 18.9 / 10.4; of 262,144 (256
-// large tiles) 13.4 / 14.2 us, where the line lies; 8192-value tiles come out
-// between the two on either side (7.0, 10.6, 15.2, 11.0 and 12.8 us).
+// small as well. The lines, from decodes out of a HIP graph in us, 16384-value
+// tiles / 4096-value tiles, by the number of the former:
+//   merge, bf16, B >= 16, n whole large tiles (128, 144, 160, 192, 224, 255):
+//     B = 64  5.6 / 5.4  5.7 / 5.9  6.0 / 6.1  6.1 / 6.2  6.3 / 6.9  6.5 / 7.2
+//     B = 512 5.8 / 5.7  6.0 / 5.9  6.2 / 6.2  6.5 / 6.3  6.6 / 7.2  6.7 / 7.3
+//   the line is 192, three small tiles for every CU (16 shards of 8,192
+//   values: 14.4 / 6.8 us for two decodes).
+//   Everything else gains up to 255, and so stays (128, 192, 252 to 255):
+//     a cut last tile, octet by octet in the large one
+//             8.8 / 6.1  8.7 / 6.9  8.7 / 8.1
+//     fp16    10.3 / 6.6  11.1 / 7.7  11.3 / 8.6
+//     the cache update alone, one shard
+//             4.5 / 3.8  4.6 / 4.2  4.7 / 4.7
+//     B = 1, 16 shards 9.8 / 5.5  10.0 / 6.1  10.1 / 6.7, which the re-read
+//             stops first where shards are large: one of 64 tiles 9.5 / 6.8,
+//             of 128 9.8 / 10.3
 constexpr uint32_t kDecOctSmall = 2;
-inline bool dec_small(uint64_t n, uint32_t nshards, uint32_t log2B) {
+inline bool dec_small(uint64_t n, uint32_t nshards, uint32_t log2B, bool f16,
+                      bool update_only) {
   constexpr uint64_t kMaxReread = uint64_t(16) << 20;
   const uint64_t groups = dec_tiles(n) * nshards;
-  return groups < 256 &&
+  const bool whole_bf16_merge =
+      log2B > 0 && !f16 && !update_only && n % kDecTile == 0;
+  return groups <= (whole_bf16_merge ? 192u : 255u) &&
          groups * (kDecOct / kDecOctSmall) * bitmap_bytes(n, log2B) / 2 <=
              kMaxReread;
 }

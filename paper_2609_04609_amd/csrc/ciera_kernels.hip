@@ -2324,7 +2324,7 @@ void launch_decode_tiles(const DecArgs &a, hipStream_t s) {
 hipError_t launch_decode(const DecArgs &a, hipStream_t s) {
   const uint64_t tiles = dec_tiles(a.n);
   if (tiles == 0 || a.nshards == 0) return hipSuccess;
-  if (dec_small(a.n, a.nshards, a.log2B)) {
+  if (dec_small(a.n, a.nshards, a.log2B, a.f16, a.out == nullptr)) {
     launch_decode_tiles<int(kDecOctSmall), true>(a, s);
     return hipGetLastError();
   }

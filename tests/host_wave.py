@@ -58,6 +58,14 @@ class HostLib:
     def order(self, waves_descend, groups_descend):
         self.lib.wave_host_order(waves_descend, groups_descend)
 
+    def dispatched(self, call):
+        """(launches, workgroups) of a call whose kernels are not run."""
+        self.lib.wave_host_dry(1)
+        call()
+        seen = self.lib.wave_host_launches(), self.lib.wave_host_groups()
+        self.lib.wave_host_dry(0)
+        return seen
+
     def workspace(self, n, R, B, ans=False):
         return buf(self.lib.ciera_workspace_bytes(
             n, R, B, self.c.WS_ANS if ans else 0))

@@ -1,0 +1,52 @@
+"""Which kernels a call launches on both sides of the size lines, counted in the
+host model without running them (tests/host_wave.py)."""
+import pytest
+
+from tests import host_wave as hw
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    lib = hw.compile_lib(str(tmp_path_factory.mktemp("host") / "libciera.so"))
+    return hw.HostLib(lib)
+
+
+TILE = 16384
+
+
+# (kind, B, R, n, values a tile has): the merge of whole large tiles turns after
+# 192 of them, what has a cut last tile, fp16 and the cache update after 255, B = 1
+# at 16 MB of bitmap bytes counted in front of the tiles
+@pytest.mark.parametrize("kind,B,R,n,tile", [
+    ("bf16", 16, 16, 12 * TILE, 4096), ("bf16", 16, 16, 13 * TILE, TILE),
+    ("bf16", 512, 192, TILE, 4096), ("bf16", 512, 193, TILE, TILE),
+    ("bf16", 4096, 1, 192 * TILE, 4096), ("bf16", 4096, 1, 193 * TILE, TILE),
+    ("bf16", 512, 16, 13 * TILE + 1, 4096),
+    ("bf16", 512, 16, 15 * TILE - 4096, 4096),
+    ("bf16", 512, 16, 16 * TILE - 1, TILE), ("bf16", 64, 255, 5, 4096),
+    ("bf16", 64, 256, 5, TILE),
+    ("fp16", 512, 16, 15 * TILE, 4096), ("fp16", 512, 16, 16 * TILE, TILE),
+    ("update", 512, 1, 255 * TILE, 4096), ("update", 512, 1, 256 * TILE, TILE),
+    ("bf16", 1, 16, 15 * TILE, 4096), ("bf16", 1, 1, 64 * TILE, 4096),
+    ("bf16", 1, 1, 65 * TILE, TILE)])
+def test_decode_tiles(host, kind, B, R, n, tile):
+    c = host.c
+    flags = c.FP16 if kind == "fp16" else 0
+    ws = host.workspace(n, R, B)
+    one = hw.buf(64)  # nothing is read: no kernel runs
+    p = one.ctypes.data
+
+    def call():
+        if kind == "update":
+            rc = host.lib.ciera_update_cache(p, p, 64, n, B, 0, ws.ctypes.data,
+                                             ws.size, None)
+        else:
+            rc = host.lib.ciera_decode_gathered(
+                p, 64, p, R, n, B, flags, p, p, ws.ctypes.data, ws.size, None)
+        assert rc == 0
+    launches, groups = host.dispatched(call)
+    tiles = R * -(-n // tile)
+    if B == 1 and tile == TILE:  # after the count kernel, four tiles a workgroup
+        assert (launches, groups) == (2, tiles + R * -(-n // (4 * tile)))
+    else:
+        assert (launches, groups) == (1, tiles)
