@@ -77,15 +77,28 @@ static_assert((kDecTile & (kDecTile - 1)) == 0 && kDecTile >= 4096,
 // Encode: one wave per tile. A tile is one 4096-value chunk (eight octets per
 // lane): whole blocks at every B.
 constexpr uint64_t kEncChunk = 4096;
-// Shards of up to this many values are encoded by one workgroup in one launch
-// (encode_small_kernel), a wave a chunk. One CU needs 4.2 us for
-// 128 values, 5.9 for 32,768 and 8.1 for 65,536, the two launches 5.4, 7.0 and
-// 7.0 (encodes back to back in a HIP graph, B = 512); with the block hash or in
-// fp16 a full round takes 9 to 10 us, and the lines cross at the same place.
+// Shards of up to kEncSmall values, in fp16 kEncSmallF16, are encoded by one
+// workgroup in one launch (encode_small_kernel), a wave a chunk. Encodes back
+// to back in a HIP graph, two launches / one, in us:
+//   values           128        32,768     40,960      49,152      57,344
+//   bf16 B = 512   5.4 / 3.9   7.1 / 5.5   7.4 / 6.2   7.4 / 6.6   7.3 / 7.5
+//        B = 64    5.2 / 3.8   6.1 / 5.5   6.7 / 6.3   6.6 / 6.6   6.7 / 7.5
+//        B = 1     5.1 / 3.6   7.6 / 5.4   8.3 / 6.1   8.1 / 6.4   9.0 / 7.1
+//   hash B = 512   6.4 / 4.9   8.7 / 6.6   8.4 / 7.7   8.9 / 7.9   8.7 / 9.3
+//        B = 64    6.0 / 4.7   7.5 / 6.4   7.4 / 7.6   7.9 / 7.7   7.7 / 9.0
+//   fp16 B = 512   5.4 / 3.9   7.8 / 6.9   8.0 / 8.3   8.2 / 8.9   8.1 / 10.3
+//        B = 64    5.2 / 3.9   6.5 / 6.7   6.8 / 8.3   7.2 / 9.0   7.0 / 10.7
+//        B = 4096  5.5 / 3.8  10.6 / 7.2  10.4 / 9.0  10.7 / 9.5  10.6 / 11.4
+// Past 8 waves a SIMD holds three, and the bit planes of fp16 keep its ALU
+// busy; at B = 4096 the exception pass of the two launches takes longer still.
 #ifndef CIERA_ENC_SMALL
 #define CIERA_ENC_SMALL 49152
 #endif
 constexpr uint64_t kEncSmall = CIERA_ENC_SMALL;
+constexpr uint64_t kEncSmallF16 = kEncSmall < 32768 ? kEncSmall : 32768;
+inline bool enc_small(uint64_t n, uint32_t log2B, bool f16) {
+  return n <= (f16 && log2B < 12 ? kEncSmallF16 : kEncSmall);
+}
 // B >= 16: the rows (B >= 512) or wave instructions (B < 512) of changed
 // exponents that one wave of the exception pass keeps in flight, and the
 // number of waves it aims for (each wave takes a run of exc_tiles_per_wave

@@ -2205,7 +2205,7 @@ hipError_t launch_encode_small(const EncArgs &a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_encode(const EncArgs &a, hipStream_t s) {
-  if (a.n <= kEncSmall) return launch_encode_small(a, s);
+  if (enc_small(a.n, a.log2B, a.f16)) return launch_encode_small(a, s);
   const dim3 grid((a.num_tiles + 3) / 4);
   const bool elems = a.log2B == 0;
   // with the fused cache update the exception pass reads the cache, not W'

@@ -79,9 +79,9 @@ def test_shared_bitmap_bytes(gu, orc, B, chunks):
 @pytest.mark.parametrize("B", [1, 16, 64, 512, 1024, 4096])
 def test_small_shards(gu, orc, B):
     """The one-workgroup encode: no value, one octet and less, the edges of
-    chunks and blocks, its largest shard (49,152 values) and the first one
-    that takes two kernels."""
+    chunks and blocks, its largest shards (32,768 and 49,152 values) and
+    the first ones that take two kernels."""
     for i, n in enumerate((0, 1, 7, 9, 4095, 4096, 4097, 8 * 4096 + 1,
-                           49_151, 49_152, 49_153)):
+                           49_151, 49_152, 49_153, 8 * 4096)):
         for k, c in enumerate((0.0, 0.003, 1.0)):
             check(gu, orc, n, B, c, 9000 + 100 * B + 3 * i + k)

@@ -14,6 +14,30 @@ def host(tmp_path_factory):
 TILE = 16384
 
 
+# one workgroup up to 49,152 values, in fp16 below B = 4096 up to 32,768
+@pytest.mark.parametrize("kind,B,line", [
+    ("exact", 1, 49_152), ("exact", 64, 49_152), ("exact", 4096, 49_152),
+    ("hash", 16, 49_152), ("hash", 512, 49_152), ("fp16", 16, 32_768),
+    ("fp16", 512, 32_768), ("fp16", 2048, 32_768), ("fp16", 4096, 49_152)])
+def test_encode_in_one_launch(host, kind, B, line):
+    c = host.c
+    ws = host.workspace(line + 1, 1, B)
+    out = hw.buf(host.lib.ciera_encoded_bound(
+        line + 1, B, c.FP16 if kind == "fp16" else 0))
+    p, o, w = hw.buf(64).ctypes.data, out.ctypes.data, ws.ctypes.data
+    for n, launches in ((line, 1), (line + 1, 2)):
+        def call():
+            if kind == "hash":
+                rc = host.lib.ciera_encode_hashed(p, p, p, n, B, o, out.size,
+                                                  None, w, ws.size, None)
+            else:
+                rc = host.lib.ciera_encode(p, p, n, B,
+                                           c.FP16 if kind == "fp16" else 0, o,
+                                           out.size, None, w, ws.size, None)
+            assert rc == 0
+        assert host.dispatched(call)[0] == launches, n
+
+
 # (kind, B, R, n, values a tile has): the merge of whole large tiles turns after
 # 192 of them, what has a cut last tile, fp16 and the cache update after 255, B = 1
 # at 16 MB of bitmap bytes counted in front of the tiles
