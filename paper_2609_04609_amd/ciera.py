@@ -202,11 +202,17 @@ def ciera_select(gains, mems, budget_bytes, flags=0):
 
 # ---- tensor-level marshalling ----
 
+# not part of torch's public interface, so a build may lack it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    """The current stream's handle. Asked for directly: the Stream object that
-    torch.cuda.current_stream() builds around it costs 2.8 us a call, as much
-    as a kernel launch; this takes 0.3."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    """The current stream's handle. Asked for directly where torch has the call
+    for it: the Stream object that torch.cuda.current_stream() builds around it
+    costs 2.8 us a call, as much as a kernel launch; this takes 0.3."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):

@@ -298,3 +298,20 @@ def test_select_ranking_hand_case(cl, orc):
         mm = rng.uniform(0.1, 5, size=k).tolist()
         b = float(rng.uniform(0, 20))
         assert cl.ciera_select(gg, mm, b) == list(orc.select(gg, mm, b))
+
+
+def test_stream_without_the_raw_handle_call(cl, monkeypatch):
+    """A torch that lacks the direct call for the stream's handle gives it
+    through the Stream object."""
+    import importlib.util
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda: types.SimpleNamespace(cuda_stream=4711))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    spec = importlib.util.spec_from_file_location("ciera_copy", cl.__file__)
+    copy = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(copy)
+    assert copy._stream() == 4711
