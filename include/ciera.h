@@ -132,8 +132,9 @@ uint64_t ciera_encoded_bound(uint64_t n_elems, uint32_t block_elems,
 
 /* Workspace bytes for encoding an n-value shard and for decoding (or cache
  * updating) `nshards` such shards at block size B (host): a 256-byte control
- * block, one 32-bit count per 4096-value encode tile and one 32-bit offset
- * per 16384-value decode tile of every shard. With
+ * block, and the larger of the encode's and the decode's 32-bit words: one
+ * per 4096 values (B > 512: per 8 blocks) and one more, or one per 16384 values
+ * of every shard and up to four more. With
  * CIERA_WS_ANS (B >= 16) it also covers ciera_ans_code on such a shard and
  * decoding rANS-coded shards: about 2.1 n bytes for coding, n per shard for
  * decoding. Returns 0 for an unsupported B or flag. */

@@ -417,9 +417,10 @@ __device__ __forceinline__ void hash_exchange(uint64_t (&x)[4], uint32_t lane,
 // and keeps the other half, so 8 values take 4 + 2 + 1 exchanges, and plain
 // xor steps finish the remaining lane bits. The first step, units i and i + 4
 // across lane bit g - 1, is taken as the units are hashed (B > 512: units 2i
-// and 2i + 1 of a block are added), so x and y hold four values here: 64
+// and 2i + 1 of a block are added), so x and y hold four values here: 60
 // VGPRs and eight waves per SIMD, against 87 and five with all sixteen terms
-// live (OLMoE shard, B = 512: 24.1 against 25.5 us for the hashed encode).
+// live (OLMoE shard, B = 512: 24.1 against 25.5 us for the hashed encode; with
+// a loop over chunks around it the pass took 121 and four).
 // With v = log2 of the values a lane holds per chunk (one per unit when
 // B <= 512, one per block above), g = log2 of the lanes sharing a block and
 // t = exchange steps, value i then belongs to local index
@@ -697,7 +698,7 @@ __device__ __forceinline__ void pad_sections(const EncArgs &a, uint32_t lane) {
 // a chunk a wave the encode of that shard (both passes) takes 25.9 instead of
 // 42.4 us, of 88.1M clustered values 84.7 instead of 92.5 us, of 4.0M values
 // 11.4 instead of 36.4 us. Without the loop over chunks the kernel also
-// needs 62 instead of 78 VGPRs (eight waves per SIMD); at B = 512 the OLMoE
+// needs 58 instead of 78 VGPRs (eight waves per SIMD); at B = 512 the OLMoE
 // shard's encode takes 23.2 instead of 23.4 us.
 constexpr int enc_waves(int cls) { return cls == kChunkBlock ? 8 : 4; }
 template <bool ELEMS, int DET, bool F16, bool NTW, int CLS>
@@ -1671,6 +1672,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
   uint16_t *const out = UPDATE_ONLY ? nullptr : a.out + uint64_t(j) * n;
 
   if (sv.mode == kModeRaw) {
+    // (decode_raw_tile is this code for B = 1: a change goes into both)
     // three streams touched once, non-temporal as in the merge: 16 shards of
     // 26.2M values decode in 374 us (encode of one included) against 395 with
     // plain accesses, of 1.06M values in 20.0 against 23.5; plain loads under
@@ -1985,7 +1987,8 @@ __global__ __launch_bounds__(kThreads) void count_tile_bits_kernel(
 }
 
 // A tile of a raw shard in the B = 1 decode: the values copied, their
-// exponents to the cache, as in decode_kernel (which keeps the code in place:
+// exponents to the cache, as in decode_kernel (a change goes into both; that
+// kernel keeps the code in place:
 // with a call here it takes 81 instead of 72 VGPRs and 2% longer on every
 // layer). 16 raw shards of 1.06M values: 21.8 us against 25.3 octet by octet.
 template <int OCT, bool UPDATE_ONLY>
