@@ -202,10 +202,16 @@ __host__ __device__ inline uint64_t dec_tiles(uint64_t n) {
 //     B = 1, 16 shards 9.8 / 5.5  10.0 / 6.1  10.1 / 6.7, which the re-read
 //             stops first where shards are large: one of 64 tiles 9.5 / 6.8,
 //             of 128 9.8 / 10.3
+// A shard of one small tile takes it whatever the number of shards: as many
+// workgroups either way (256 shards of 500 values, B = 512: 4.8 us octet by
+// octet with element-wise accesses, 5.2 in a large tile, 4.7; of 4,096 values
+// 8.0 / 3.8).
 constexpr uint32_t kDecOctSmall = 2;
+constexpr uint64_t kDecTileSmall = uint64_t(kThreads) * 8 * kDecOctSmall;
 inline bool dec_small(uint64_t n, uint32_t nshards, uint32_t log2B, bool f16,
                       bool update_only) {
   constexpr uint64_t kMaxReread = uint64_t(16) << 20;
+  if (n <= kDecTileSmall) return true;
   const uint64_t groups = dec_tiles(n) * nshards;
   const bool whole_bf16_merge =
       log2B > 0 && !f16 && !update_only && n % kDecTile == 0;

@@ -59,10 +59,14 @@ class HostLib:
         self.lib.wave_host_order(waves_descend, groups_descend)
 
     def dispatched(self, call):
-        """(launches, workgroups) of a call whose kernels are not run."""
+        """(launches, workgroups, the last kernel's address) of a call whose
+        kernels are not run."""
         self.lib.wave_host_dry(1)
         call()
-        seen = self.lib.wave_host_launches(), self.lib.wave_host_groups()
+        last = self.lib.wave_host_last_kernel
+        last.restype = ctypes.c_void_p
+        seen = (self.lib.wave_host_launches(), self.lib.wave_host_groups(),
+                last())
         self.lib.wave_host_dry(0)
         return seen
 

@@ -69,6 +69,7 @@ inline char *stacks;
 inline bool waves_descend, groups_descend;
 inline uint32_t max_groups = ~0u;  // run only this many of a launch's groups
 inline uint32_t launches, groups_launched;  // since they were last cleared
+inline void *last_kernel;
 
 inline void yield(State s) {
   Fiber &f = fibers[current];
@@ -291,6 +292,7 @@ void hipLaunchKernelGGL(void (*k)(P...), dim3 grid, dim3 block, uint32_t,
   blockDim = block;
   const uint64_t groups = uint64_t(grid.x) * grid.y;
   ++wave_host::launches;
+  wave_host::last_kernel = reinterpret_cast<void *>(k);
   wave_host::groups_launched += uint32_t(groups);
   for (uint64_t i = 0; i < groups && i < wave_host::max_groups; ++i) {
     const uint64_t g = wave_host::groups_descend ? groups - 1 - i : i;

@@ -14,3 +14,4 @@ extern "C" void wave_host_dry(int dry) {
 }
 extern "C" uint32_t wave_host_launches() { return wave_host::launches; }
 extern "C" uint32_t wave_host_groups() { return wave_host::groups_launched; }
+extern "C" void *wave_host_last_kernel() { return wave_host::last_kernel; }

@@ -21,12 +21,13 @@ def gu():
 
 
 # (shards, values per shard): 16384-value tiles times shards reaches 256 from
-# the eighth to the thirteenth; the last two lie on both sides of 192 whole
-# tiles, where bf16 with B >= 16 turns
+# the eighth to the thirteenth; the next two lie on both sides of 192 whole
+# tiles, where bf16 with B >= 16 turns; the last are one small tile a shard
 SHAPES = [(1, 1), (5, 4095), (5, 4096), (4, 4097), (16, 16_385),
           (3, 12 * 4096 + 9), (255, 16_384), (256, 16_384), (256, 16_381),
           (4, 1_048_577), (4, 1_064_960), (1, 255 * 16_384 + 1),
-          (2, 3_000_001), (12, 262_144), (193, 16_384)]
+          (2, 3_000_001), (12, 262_144), (193, 16_384),
+          (300, 501), (257, 4096)]
 
 
 @pytest.mark.parametrize("fp16", [False, True])

@@ -48,14 +48,22 @@ def test_encode_in_one_launch(host, kind, B, line):
     ("bf16", 512, 16, 13 * TILE + 1, 4096),
     ("bf16", 512, 16, 15 * TILE - 4096, 4096),
     ("bf16", 512, 16, 16 * TILE - 1, TILE), ("bf16", 64, 255, 5, 4096),
-    ("bf16", 64, 256, 5, TILE),
+    ("bf16", 64, 256, 4097, TILE),
     ("fp16", 512, 16, 15 * TILE, 4096), ("fp16", 512, 16, 16 * TILE, TILE),
     ("update", 512, 1, 255 * TILE, 4096), ("update", 512, 1, 256 * TILE, TILE),
     ("bf16", 1, 16, 15 * TILE, 4096), ("bf16", 1, 1, 64 * TILE, 4096),
     ("bf16", 1, 1, 65 * TILE, TILE)])
 def test_decode_tiles(host, kind, B, R, n, tile):
-    c = host.c
-    flags = c.FP16 if kind == "fp16" else 0
+    launches, groups, _ = host.dispatched(decode_call(host, kind, B, R, n))
+    tiles = R * -(-n // tile)
+    if B == 1 and tile == TILE:  # after the count kernel, four tiles a workgroup
+        assert (launches, groups) == (2, tiles + R * -(-n // (4 * tile)))
+    else:
+        assert (launches, groups) == (1, tiles)
+
+
+def decode_call(host, kind, B, R, n):
+    flags = host.c.FP16 if kind == "fp16" else 0
     ws = host.workspace(n, R, B)
     one = hw.buf(64)  # nothing is read: no kernel runs
     p = one.ctypes.data
@@ -67,10 +75,18 @@ def test_decode_tiles(host, kind, B, R, n, tile):
         else:
             rc = host.lib.ciera_decode_gathered(
                 p, 64, p, R, n, B, flags, p, p, ws.ctypes.data, ws.size, None)
-        assert rc == 0
-    launches, groups = host.dispatched(call)
-    tiles = R * -(-n // tile)
-    if B == 1 and tile == TILE:  # after the count kernel, four tiles a workgroup
-        assert (launches, groups) == (2, tiles + R * -(-n // (4 * tile)))
-    else:
-        assert (launches, groups) == (1, tiles)
+        assert rc == 0 and one is not None
+    return call
+
+
+@pytest.mark.parametrize("kind,B", [("bf16", 1), ("bf16", 16), ("bf16", 4096),
+                                    ("fp16", 512)])
+def test_one_small_tile_a_shard(host, kind, B):
+    """Shards of up to 4096 values take the small tile's kernel at any number
+    of shards, longer ones up to 255 large tiles."""
+    def kernel(R, n):
+        return host.dispatched(decode_call(host, kind, B, R, n))[2]
+    small = kernel(1, 5)
+    assert kernel(256, 5) == kernel(256, 4096) == kernel(65_535, 500) == small
+    assert kernel(255, 4097) == small
+    assert kernel(256, 4097) != small
