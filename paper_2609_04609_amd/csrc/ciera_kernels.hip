@@ -182,6 +182,11 @@ __device__ __forceinline__ void st16(uint16_t *p, uint4 v) {
   *reinterpret_cast<u32x4_t *>(p) = x;
 }
 
+// Around the plain loads of a branch whose other side has non-temporal ones:
+// the compiler would otherwise take the two for the same loads and merge them
+// into plain ones.
+__device__ __forceinline__ void keep_branch() { asm volatile("" ::: "memory"); }
+
 // ------------------------------------------------- octet loads and stores --
 // `valid` is the number of in-range values of the octet (1..8); the ragged
 // last octet of a shard goes element by element.
@@ -1458,8 +1463,9 @@ __global__ __launch_bounds__(64 * kSmallWaves) void encode_small_kernel(
 }
 
 // Raw form: header + the values unchanged. One octet per lane, non-temporal:
-// 26.2M values, with the decode of that shard, take 43.9 us against 49.5 with
-// plain accesses.
+// 25.2M values just written and then encoded take 30.1 us together, against
+// 35.8 with plain accesses (34.0M 40.7 / 49.1; encoded again, out of the cache,
+// 22.6 / 21.6).
 __global__ __launch_bounds__(kThreads) void encode_raw_kernel(
     const uint16_t *w, uint64_t n, uint32_t B, uint8_t *out,
     uint64_t *out_bytes, uint32_t dtype) {
@@ -1673,19 +1679,25 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
 
   if (sv.mode == kModeRaw) {
     // (decode_raw_tile is this code for B = 1: a change goes into both)
-    // three streams touched once, non-temporal as in the merge: 16 shards of
-    // 26.2M values decode in 374 us (encode of one included) against 395 with
-    // plain accesses, of 1.06M values in 20.0 against 23.5; plain loads under
-    // non-temporal stores win while the gather fits the Infinity Cache from
-    // one call to the next (19.4 us), and lose beyond (389)
+    // three streams touched once: non-temporal as in the merge, but for the
+    // loads of a gather that may lie in the Infinity Cache
     const uint16_t *body =
         reinterpret_cast<const uint16_t *>(sv.enc + kHeaderBytes);
     if (full) {
       uint4 wv[OCT];
+      if (raw_plain_loads(n, a.nshards)) {
+        keep_branch();
 #pragma unroll
-      for (int u = 0; u < OCT; ++u)
-        wv[u] = ld_nt16(body + base +
-                        (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+        for (int u = 0; u < OCT; ++u)
+          wv[u] = ld16(body + base +
+                       (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+        keep_branch();
+      } else {
+#pragma unroll
+        for (int u = 0; u < OCT; ++u)
+          wv[u] = ld_nt16(body + base +
+                          (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+      }
 #pragma unroll
       for (int u = 0; u < OCT; ++u) {
         const uint64_t elem =
@@ -1990,21 +2002,31 @@ __global__ __launch_bounds__(kThreads) void count_tile_bits_kernel(
 // exponents to the cache, as in decode_kernel (a change goes into both; that
 // kernel keeps the code in place:
 // with a call here it takes 81 instead of 72 VGPRs and 2% longer on every
-// layer). 16 raw shards of 1.06M values: 21.8 us against 25.3 octet by octet.
+// layer). 16 raw shards of 1.06M values: 18.0 us against 21.9 octet by octet.
 template <int OCT, bool UPDATE_ONLY>
 __device__ __forceinline__ void decode_raw_tile(const ShardView &sv,
                                                 uint64_t base, uint64_t n,
-                                                bool full, int wave, int lane,
+                                                bool full, bool plain,
+                                                int wave, int lane,
                                                 uint8_t *cache,
                                                 uint16_t *out) {
   const uint16_t *body =
       reinterpret_cast<const uint16_t *>(sv.enc + kHeaderBytes);
   if (full) {
     uint4 wv[OCT];
+    if (plain) {
+      keep_branch();
 #pragma unroll
-    for (int u = 0; u < OCT; ++u)
-      wv[u] = ld_nt16(body + base +
-                      (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+      for (int u = 0; u < OCT; ++u)
+        wv[u] = ld16(body + base +
+                     (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+      keep_branch();
+    } else {
+#pragma unroll
+      for (int u = 0; u < OCT; ++u)
+        wv[u] = ld_nt16(body + base +
+                        (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+    }
 #pragma unroll
     for (int u = 0; u < OCT; ++u) {
       const uint64_t elem =
@@ -2053,8 +2075,9 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
   uint16_t *const out = UPDATE_ONLY ? nullptr : a.out + uint64_t(j) * n;
 
   if (sv.mode == kModeRaw) {
-    decode_raw_tile<OCT, UPDATE_ONLY>(sv, base, n, base + T <= n, wave, lane,
-                                      cache, out);
+    decode_raw_tile<OCT, UPDATE_ONLY>(sv, base, n, base + T <= n,
+                                      raw_plain_loads(n, a.nshards), wave,
+                                      lane, cache, out);
     return;
   }
 

@@ -86,3 +86,35 @@ def test_decode_tile_edges(gu, orc, B, fp16):
                                  fp16=fp16)
             np.testing.assert_array_equal(gu.host_u8(c), e2[own], err_msg=msg)
         assert ws.error() == 0, msg
+
+
+# a gather of raw shards on both sides of 192 MB of values, where the loads of
+# its values turn non-temporal; whole and cut last tiles
+@pytest.mark.parametrize("fp16,B", [(False, 1), (False, 512), (True, 512)])
+@pytest.mark.parametrize("n", [6_291_455, 6_291_456, 6_291_457])
+def test_raw_gather_on_both_sides_of_the_cache(gu, n, fp16, B):
+    from paper_2609_04609_amd import ciera
+    R = 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + B)
+    w = torch.randint(-32768, 32768, (R * n,), dtype=torch.int16,
+                      device="cuda", generator=g)
+    flags = ciera.FP16 if fp16 else 0
+    bound = int(ciera.ciera_encoded_bound(n, B, flags))
+    buf = torch.empty(R * bound, dtype=torch.uint8, device="cuda")
+    offs = torch.arange(R, dtype=torch.int64, device="cuda") * bound
+    ws = ciera.Workspace(n, R, B)
+    for j in range(R):
+        ciera.encode_t(w[j * n:(j + 1) * n], None, B, ws,
+                       buf[j * bound:(j + 1) * bound], raw=True, fp16=fp16)
+    out = torch.zeros_like(w)
+    cache = torch.full((R * n,), 0x5A, dtype=torch.uint8, device="cuda")
+    ciera.decode_gathered_t(buf, offs, n, B, out, cache, ws, fp16=fp16)
+    assert torch.equal(out, w)
+    x = w.to(torch.int32)
+    assert torch.equal(cache, ((x >> 10) & 31 if fp16 else (x >> 7) & 255)
+                       .to(torch.uint8))
+    one = torch.full((n,), 0x5A, dtype=torch.uint8, device="cuda")
+    ciera.update_cache_t(one, buf[:bound], n, B, ws, fp16=fp16)
+    assert torch.equal(one, cache[:n])
+    assert ws.error() == 0
