@@ -222,14 +222,14 @@ inline bool dec_small(uint64_t n, uint32_t nshards, uint32_t log2B, bool f16,
 // Raw shards: plain loads while the values of the whole gather stay below
 // this, non-temporal ones above; the stores are non-temporal either way. A
 // gather that has just arrived, or was decoded before, still lies in the 256 MB
-// Infinity Cache. Decodes of raw shards in us, all plain / non-temporal loads /
+// Infinity Cache. (Small layers always have plain ones.) Decodes of raw shards in us, all plain / non-temporal loads /
 // this, with the gather just copied there, decoded again, and long evicted:
 //   R = 1,  16.8M values (34 MB)   14.3 / 15.9 / 13.9  14.9 / 15.8 / 13.5  20.6 / 17.7 / 18.2
 //   R = 16,  3.0M values (96 MB)   45.5 / 39.6 / 35.0  38.0 / 43.4 / 38.9  48.7 / 44.7 / 45.3
 //   R = 1,  88.1M values (176 MB)  80.2 / 74.5 / 65.6  82.8 / 76.4 / 66.1  84.9 / 78.9 / 80.1
 //   R = 16,  8.4M values (268 MB)  119 / 112 / 125     123 / 113 / 99      125 / 115 / 119
 constexpr uint64_t kRawPlainBytes = uint64_t(192) << 20;
-__host__ __device__ inline bool raw_plain_loads(uint64_t n, uint32_t nshards) {
+inline bool raw_plain_loads(uint64_t n, uint32_t nshards) {
   return 2 * n * nshards <= kRawPlainBytes;
 }
 // decode: per-shard count segments (tiles + total), 16-byte aligned

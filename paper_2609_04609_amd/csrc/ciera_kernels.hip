@@ -182,11 +182,6 @@ __device__ __forceinline__ void st16(uint16_t *p, uint4 v) {
   *reinterpret_cast<u32x4_t *>(p) = x;
 }
 
-// Around the plain loads of a branch whose other side has non-temporal ones:
-// the compiler would otherwise take the two for the same loads and merge them
-// into plain ones.
-__device__ __forceinline__ void keep_branch() { asm volatile("" ::: "memory"); }
-
 // ------------------------------------------------- octet loads and stores --
 // `valid` is the number of in-range values of the octet (1..8); the ragged
 // last octet of a shard goes element by element.
@@ -1634,8 +1629,10 @@ __global__ __launch_bounds__(kScanThreads) void tile_prefix_kernel(DecArgs a) {
 // A whole tile issues its loads in two batches (sign|mantissa bytes together
 // with the bitmap words, then one cache-or-exception load per octet, chosen
 // by address rather than by branch); the ragged last tile goes octet by
-// octet.
-template <int OCT, bool UPDATE_ONLY, bool F16 = false>
+// octet. RAWNT: the loads of raw shards (raw_plain_loads); a template argument,
+// because a branch on it moved the schedule of the merge (fp16, 16 shards of
+// 2.1M values: 31.4 -> 36.8 us).
+template <int OCT, bool UPDATE_ONLY, bool F16, bool RAWNT>
 __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
   constexpr uint32_t T = kThreads * 8 * OCT;
   // tile bitmap words (32 blocks each) covering at most T/16 blocks + 1 word
@@ -1685,18 +1682,11 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecArgs a) {
         reinterpret_cast<const uint16_t *>(sv.enc + kHeaderBytes);
     if (full) {
       uint4 wv[OCT];
-      if (raw_plain_loads(n, a.nshards)) {
-        keep_branch();
 #pragma unroll
-        for (int u = 0; u < OCT; ++u)
-          wv[u] = ld16(body + base +
-                       (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
-        keep_branch();
-      } else {
-#pragma unroll
-        for (int u = 0; u < OCT; ++u)
-          wv[u] = ld_nt16(body + base +
-                          (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+      for (int u = 0; u < OCT; ++u) {
+        const uint16_t *const p =
+            body + base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u;
+        wv[u] = RAWNT ? ld_nt16(p) : ld16(p);
       }
 #pragma unroll
       for (int u = 0; u < OCT; ++u) {
@@ -2003,29 +1993,21 @@ __global__ __launch_bounds__(kThreads) void count_tile_bits_kernel(
 // kernel keeps the code in place:
 // with a call here it takes 81 instead of 72 VGPRs and 2% longer on every
 // layer). 16 raw shards of 1.06M values: 18.0 us against 21.9 octet by octet.
-template <int OCT, bool UPDATE_ONLY>
+template <int OCT, bool UPDATE_ONLY, bool RAWNT>
 __device__ __forceinline__ void decode_raw_tile(const ShardView &sv,
                                                 uint64_t base, uint64_t n,
-                                                bool full, bool plain,
-                                                int wave, int lane,
+                                                bool full, int wave, int lane,
                                                 uint8_t *cache,
                                                 uint16_t *out) {
   const uint16_t *body =
       reinterpret_cast<const uint16_t *>(sv.enc + kHeaderBytes);
   if (full) {
     uint4 wv[OCT];
-    if (plain) {
-      keep_branch();
 #pragma unroll
-      for (int u = 0; u < OCT; ++u)
-        wv[u] = ld16(body + base +
-                     (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
-      keep_branch();
-    } else {
-#pragma unroll
-      for (int u = 0; u < OCT; ++u)
-        wv[u] = ld_nt16(body + base +
-                        (uint64_t(wave * OCT + u) * 64u + lane) * 8u);
+    for (int u = 0; u < OCT; ++u) {
+      const uint16_t *const p =
+          body + base + (uint64_t(wave * OCT + u) * 64u + lane) * 8u;
+      wv[u] = RAWNT ? ld_nt16(p) : ld16(p);
     }
 #pragma unroll
     for (int u = 0; u < OCT; ++u) {
@@ -2057,7 +2039,7 @@ __device__ __forceinline__ void decode_raw_tile(const ShardView &sv,
 // Decode, B = 1, step 2 (step 3 after a scan of the counts): patch and merge
 // (UPDATE_ONLY: patch only; SMALL: the only step, the tile counts the bitmap
 // in front of it).
-template <int OCT, bool UPDATE_ONLY, bool SMALL>
+template <int OCT, bool UPDATE_ONLY, bool SMALL, bool RAWNT>
 __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
   constexpr uint32_t T = kThreads * 8 * OCT;
   __shared__ uint32_t s_seg[4 * OCT + 1];
@@ -2075,9 +2057,8 @@ __global__ __launch_bounds__(kThreads) void decode_elems_kernel(DecArgs a) {
   uint16_t *const out = UPDATE_ONLY ? nullptr : a.out + uint64_t(j) * n;
 
   if (sv.mode == kModeRaw) {
-    decode_raw_tile<OCT, UPDATE_ONLY>(sv, base, n, base + T <= n,
-                                      raw_plain_loads(n, a.nshards), wave,
-                                      lane, cache, out);
+    decode_raw_tile<OCT, UPDATE_ONLY, RAWNT>(sv, base, n, base + T <= n, wave,
+                                             lane, cache, out);
     return;
   }
 
@@ -2319,31 +2300,21 @@ hipError_t launch_encode_raw(const uint16_t *w, uint64_t n, uint32_t B,
 }
 
 namespace {
-template <int OCT, bool SMALL>
+template <int OCT, bool SMALL, bool RAWNT>
 void launch_decode_tiles(const DecArgs &a, hipStream_t s) {
   constexpr uint64_t T = uint64_t(kThreads) * 8 * OCT;
-  const dim3 grid(uint32_t((a.n + T - 1) / T), a.nshards), block(kThreads);
-  const bool upd = a.out == nullptr;
-  if (a.log2B == 0) {
-    if (upd)
-      hipLaunchKernelGGL((decode_elems_kernel<OCT, true, SMALL>), grid, block,
-                         0, s, a);
-    else
-      hipLaunchKernelGGL((decode_elems_kernel<OCT, false, SMALL>), grid, block,
-                         0, s, a);
-  } else if (a.f16) {
-    if (upd)
-      hipLaunchKernelGGL((decode_kernel<OCT, true, true>), grid, block, 0, s,
-                         a);
-    else
-      hipLaunchKernelGGL((decode_kernel<OCT, false, true>), grid, block, 0, s,
-                         a);
-  } else {
-    if (upd)
-      hipLaunchKernelGGL((decode_kernel<OCT, true>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((decode_kernel<OCT, false>), grid, block, 0, s, a);
-  }
+  const dim3 grid(uint32_t((a.n + T - 1) / T), a.nshards);
+  auto go = [&](auto upd) {
+    constexpr bool U = decltype(upd)::value;
+    auto k = a.log2B == 0 ? decode_elems_kernel<OCT, U, SMALL, RAWNT>
+             : a.f16      ? decode_kernel<OCT, U, true, RAWNT>
+                          : decode_kernel<OCT, U, false, RAWNT>;
+    hipLaunchKernelGGL(k, grid, dim3(kThreads), 0, s, a);
+  };
+  if (a.out == nullptr)
+    go(bool_c<true>{});
+  else
+    go(bool_c<false>{});
 }
 }  // namespace
 
@@ -2351,7 +2322,7 @@ hipError_t launch_decode(const DecArgs &a, hipStream_t s) {
   const uint64_t tiles = dec_tiles(a.n);
   if (tiles == 0 || a.nshards == 0) return hipSuccess;
   if (dec_small(a.n, a.nshards, a.log2B, a.f16, a.out == nullptr)) {
-    launch_decode_tiles<int(kDecOctSmall), true>(a, s);
+    launch_decode_tiles<int(kDecOctSmall), true, false>(a, s);
     return hipGetLastError();
   }
   if (a.log2B == 0) {
@@ -2366,7 +2337,10 @@ hipError_t launch_decode(const DecArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(tile_prefix_kernel, dim3(a.nshards), dim3(kScanThreads),
                        0, s, a);
   }
-  launch_decode_tiles<int(kDecOct), false>(a, s);
+  if (raw_plain_loads(a.n, a.nshards))
+    launch_decode_tiles<int(kDecOct), false, false>(a, s);
+  else
+    launch_decode_tiles<int(kDecOct), false, true>(a, s);
   return hipGetLastError();
 }
 
