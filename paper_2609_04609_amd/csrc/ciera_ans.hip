@@ -468,12 +468,12 @@ __global__ __launch_bounds__(kThreads) void ans_copy_kernel(AnsEncArgs a) {
   }
 }
 
-// All of it for shards of up to kAnsSmallChunks chunks (65,536 values), a wave a
-// chunk. One CU's time grows with the exceptions, so with the share of blocks
+// All of it for shards of up to kAnsSmallChunks chunks (65,536 values), a wave
+// a chunk. One CU's time grows with the exceptions, so with the share of blocks
 // that changed. Three launches / one from a HIP graph, in us:
-//   values                        16,384       32,768       49,152       65,536
-//   40 to 50% of blocks changed  14.7 / 11.5  16.5 / 12.2  18.6 / 13.9  18.0 / 14.2
-//   all of them                  16.4 / 12.4  18.1 / 15.5  18.7 / 17.9  18.6 / 21.0
+//   values                  16,384       32,768       49,152       65,536
+//   40 to 50% changed    14.7 / 11.5  16.5 / 12.2  18.6 / 13.9  18.0 / 14.2
+//   all changed          16.4 / 12.4  18.1 / 15.5  18.7 / 17.9  18.6 / 21.0
 // The line is a workgroup's 16 waves: tensors that keep about half of their
 // blocks gain on all of the range, those that keep none up to 49,152 values.
 constexpr uint32_t kAnsSmallChunks = 16;

@@ -222,12 +222,13 @@ inline bool dec_small(uint64_t n, uint32_t nshards, uint32_t log2B, bool f16,
 // Raw shards: plain loads while the values of the whole gather stay below
 // this, non-temporal ones above; the stores are non-temporal either way. A
 // gather that has just arrived, or was decoded before, still lies in the 256 MB
-// Infinity Cache. (Small layers always have plain ones.) Decodes of raw shards in us, all plain / non-temporal loads /
-// this, with the gather just copied there, decoded again, and long evicted:
-//   R = 1,  16.8M values (34 MB)   14.3 / 15.9 / 13.9  14.9 / 15.8 / 13.5  20.6 / 17.7 / 18.2
-//   R = 16,  3.0M values (96 MB)   45.5 / 39.6 / 35.0  38.0 / 43.4 / 38.9  48.7 / 44.7 / 45.3
-//   R = 1,  88.1M values (176 MB)  80.2 / 74.5 / 65.6  82.8 / 76.4 / 66.1  84.9 / 78.9 / 80.1
-//   R = 16,  8.4M values (268 MB)  119 / 112 / 125     123 / 113 / 99      125 / 115 / 119
+// Infinity Cache. (Small layers always have plain ones.) Decodes in us, all
+// accesses plain / all non-temporal / plain loads, of a gather
+//                         just copied there  decoded again      evicted
+//   1 x 16.8M   (34 MB)   14.4/15.8/13.8     14.8/15.7/13.5     20.0/17.7/18.1
+//   16 x 3.0M   (96 MB)   43.9/39.3/34.7     37.9/43.2/39.0     46.9/44.7/45.4
+//   1 x 88.1M  (176 MB)   78.4/74.3/65.5     80.4/76.1/66.2     80.4/78.6/79.8
+//   16 x 8.4M  (268 MB)    117/111/126        121/114/100        121/116/119
 constexpr uint64_t kRawPlainBytes = uint64_t(192) << 20;
 inline bool raw_plain_loads(uint64_t n, uint32_t nshards) {
   return 2 * n * nshards <= kRawPlainBytes;
