@@ -65,15 +65,15 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
 }
 
 // Workgroup-wide sum and exclusive scan of one value per thread, NW waves.
-template <int NW, typename T>
-__device__ T block_sum(T v, T *s_red) {
+template <int NW>
+__device__ uint32_t block_sum32(uint32_t v, uint32_t *s_red) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   __syncthreads();
   if (lane == 0) s_red[wave] = v;
   __syncthreads();
-  T t = 0;
+  uint32_t t = 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) t += s_red[w];
   return t;
@@ -214,7 +214,7 @@ __device__ __forceinline__ uint32_t quantise(uint32_t h, uint64_t E,
     const uint64_t q = (uint64_t(h) << kAnsScale) / E;
     f = q ? uint32_t(q) : 1u;
   }
-  uint32_t sum = block_sum<NW>(f, t.red);
+  uint32_t sum = block_sum32<NW>(f, t.red);
   if (sum < kAnsM) {
     const uint32_t best = block_argmax<NW>(h, s, t.key);
     if (s == best) f += kAnsM - sum;
@@ -416,7 +416,6 @@ __device__ __forceinline__ void put_section(const AnsEncArgs &a, uint32_t K,
 __global__ __launch_bounds__(kThreads) void ans_copy_kernel(AnsEncArgs a) {
   constexpr int NW = kThreads / 64;
   __shared__ uint32_t s_red[NW];
-  __shared__ uint64_t s_red64[NW];
   __shared__ uint32_t s_start[kThreads + 1];
   const uint32_t tid = threadIdx.x;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -429,20 +428,22 @@ __global__ __launch_bounds__(kThreads) void ans_copy_kernel(AnsEncArgs a) {
   const uint32_t per = (K + gridDim.x - 1) / gridDim.x;
   const uint32_t k0 = min(blockIdx.x * per, K), k1 = min(k0 + per, K);
   if (k0 == k1 && blockIdx.x) return;
-  // stream bytes in front of k0, and in all: a list of nearly 2^32 bytes that
-  // does not compress passes 2^32 there. Offsets fit 32 bits once C < E.
-  uint32_t front = 0;
-  uint64_t all = 0;
+  // stream dwords in front of k0, and in all. In bytes the sum of a list of
+  // nearly 2^32 that does not compress would pass 2^32; streams are whole
+  // dwords, and 2^20 of at most kAnsStreamMax bytes stay below that. Byte
+  // offsets fit 32 bits once C < E.
+  static_assert((kAnsStreamMax / 4ull) << 20 < 1ull << 32, "sum in dwords");
+  uint32_t front = 0, all = 0;
 #pragma unroll 8
   for (uint32_t c = tid; c < K; c += kThreads) {
-    const uint32_t b = stream_bytes(a.counts[c]);
-    all += b;
-    front += c < k0 ? b : 0u;
+    const uint32_t d = stream_bytes(a.counts[c]) >> 2;
+    all += d;
+    front += c < k0 ? d : 0u;
   }
-  all = block_sum<NW>(all, s_red64);
-  front = block_sum<NW>(front, s_red);
+  all = block_sum32<NW>(all, s_red);
+  front = 4u * block_sum32<NW>(front, s_red);
   const uint64_t E = ld64(a.enc + 32);
-  const uint64_t C = kAnsFixed + 4ull * K + all;
+  const uint64_t C = kAnsFixed + 4ull * K + 4ull * all;
   if (C >= E) {
     if (blockIdx.x == 0 && tid == 0 && a.out_bytes)
       *a.out_bytes = ld64(a.enc + 48);
