@@ -51,15 +51,15 @@ KERNEL_SRC = [os.path.join(ROOT, "paper_2609_04609_amd", "csrc", f)
 # scaled by what the counters read for a 1 GiB copy) for the sources whose
 # concatenation has this sha256; see profiles/hbm_traffic_*.md. Reported only
 # while those sources are unchanged.
-_SRC_SHA = "b9c8a4c87501c7e80e9d08cb553b2ca932d33f41e2e8fc9620b077ca38630e1b"
+_SRC_SHA = "0ddf4b626896bb4f1c5a44c7a452205e47a080741831bd7a2a3fce9fc9519897"
 MEASURED_TRAFFIC = {
     # ciera_decode_gathered (tile_prefix_kernel + decode_kernel) and the
     # fused-update ciera_encode (encode_pass_kernel + encode_exc_rows_kernel)
-    ("dsv3_layer", 512, "bf16"): {"sha": _SRC_SHA, "decode": 48925697073,
-                                  "encode": 423549901},
+    ("dsv3_layer", 512, "bf16"): {"sha": _SRC_SHA, "decode": 48924703343,
+                                  "encode": 423560146},
     ("olmoe_layer_c0.1", 512, "bf16"): {"sha": _SRC_SHA,
-                                        "decode": 1778723470,
-                                        "encode": 123691340},
+                                        "decode": 1778728484,
+                                        "encode": 123695868},
 }
 
 
